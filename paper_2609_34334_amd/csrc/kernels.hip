@@ -48,10 +48,11 @@ struct TI32 {
     static __device__ __forceinline__ uint32_t narrow(uint32_t v) { return v; }
 };
 
-// VE elements in one vector register group; aligned to its size (at most
-// 16 bytes) so that it loads as one 8- or 16-byte access per piece.
+// VE elements in one vector register group.  It is aligned like its element
+// only: ldp and stp below move it in 8- or 16-byte accesses at any element
+// address.
 template <typename S, int VE>
-struct alignas(sizeof(S) * VE < 16 ? sizeof(S) * VE : 16) Pack {
+struct Pack {
     S v[VE];
 };
 
@@ -112,8 +113,16 @@ constexpr int kVeBf16Partial = 4;
 constexpr int kVeBf16Only = 8;
 constexpr int kVe32 = 4;
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// Byte-aligned vectors.  The compute units take a 16-byte global access at any
+// byte address (the HSA target runs with unaligned access enabled), so the
+// same instruction serves aligned and misaligned operands.  A misaligned
+// stream costs almost nothing where HBM is the limit, as a wave's 1 KiB span
+// only touches one line more: the bf16 fold into shards of odd length takes
+// 27.3 us at R = 6, n = 1,398,103 (26.8 for n + 1) and 78.1 us at R = 8,
+// n = 3,145,727 (77.3), where an element-by-element fallback took 62.5 and
+// 98.6; four fused ring hops of the latter take 104 us instead of 170.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(1)));
 
 // Vector load / store of a Pack in 16-byte pieces (8 bytes for an 8-byte
 // Pack), optionally non-temporal.
@@ -186,13 +195,12 @@ __device__ __forceinline__ void reduce_segment(const RSegArg &s, int lb, int nb)
     SO *out = (SO *)s.out;
     const uint64_t n = s.n;
 
-    // Elements before in1 reaches 16-byte alignment; the vector body needs
-    // in0, in1 and out all 16-byte aligned at the same element.
+    // Elements before in1 reaches 16-byte alignment.  in0 and out mostly
+    // reach it at the same element; where they do not (the ring's last step
+    // into an output shard whose length is odd), their vectors are
+    // misaligned.
     uint64_t h = ((16u - ((uintptr_t)in1 & 15u)) & 15u) / sizeof(S1);
     if (h > n) h = n;
-    const bool vec = ((((uintptr_t)(in0 + h)) | ((uintptr_t)(in1 + h)) | ((uintptr_t)(out + h))) &
-                      15u) == 0;
-    if (!vec) h = n;
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
@@ -280,13 +288,9 @@ __device__ __forceinline__ void multihop_segment(const MSegArg &s, int lb, int n
     for (int m = 0; m < MAXL; ++m) loc[m] = m < nl ? (const S1 *)s.loc[m] : (const S1 *)s.loc[0];
 
     // Elements before the first contribution reaches 16-byte alignment; the
-    // vector body needs every operand 16-byte aligned at the same element.
+    // operands that do not reach it there are read or written misaligned.
     uint64_t h = ((16u - ((uintptr_t)loc[0] & 15u)) & 15u) / sizeof(S1);
     if (h > n) h = n;
-    uintptr_t mis = (uintptr_t)(in0 + h) | (uintptr_t)(out + h);
-#pragma unroll
-    for (int m = 0; m < MAXL; ++m) mis |= (uintptr_t)(loc[m] + h);
-    if (mis & 15u) h = n;
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
@@ -403,12 +407,11 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
     const int nout = a.write_all ? R : 1;
     auto dst = [&](int q) -> S * { return (S *)a.out[a.write_all ? q : j] + oe; };
 
+    // Elements before the first operand reaches 16-byte alignment.  A chunk
+    // of odd length leaves the inputs' phase and the output shard's apart: the
+    // reads are kept aligned (R streams) and the one write is misaligned.
     uint64_t h = ((16u - ((uintptr_t)src(0) & 15u)) & 15u) / sizeof(S);
     if (h > n) h = n;
-    uintptr_t mis = 0;
-    for (int k = 0; k < R; ++k) mis |= (uintptr_t)(src(k) + h);
-    for (int q = 0; q < nout; ++q) mis |= (uintptr_t)(dst(q) + h);
-    if (mis & 15u) h = n;
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
@@ -469,7 +472,7 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
         {
             constexpr int KB = 8;
             {
-                P v0 = ((const P *)(src(0) + h))[i];
+                P v0 = ldp<false>((const P *)(src(0) + h) + i);
 #pragma unroll
                 for (int e = 0; e < VE; ++e) acc[e] = T::widen(v0.v[e]);
             }
@@ -477,14 +480,14 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
             for (; k + KB <= R; k += KB) {
                 P v[KB];
 #pragma unroll
-                for (int q = 0; q < KB; ++q) v[q] = ((const P *)(src(k + q) + h))[i];
+                for (int q = 0; q < KB; ++q) v[q] = ldp<false>((const P *)(src(k + q) + h) + i);
 #pragma unroll
                 for (int q = 0; q < KB; ++q)
 #pragma unroll
                     for (int e = 0; e < VE; ++e) acc[e] = add(acc[e], v[q].v[e]);
             }
             for (; k < R; ++k) {
-                P v = ((const P *)(src(k) + h))[i];
+                P v = ldp<false>((const P *)(src(k) + h) + i);
 #pragma unroll
                 for (int e = 0; e < VE; ++e) acc[e] = add(acc[e], v.v[e]);
             }
@@ -492,7 +495,7 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
         P y;
 #pragma unroll
         for (int e = 0; e < VE; ++e) y.v[e] = T::narrow(acc[e]);
-        for (int q = 0; q < nout; ++q) ((P *)(dst(q) + h))[i] = y;
+        for (int q = 0; q < nout; ++q) stp<false>((P *)(dst(q) + h) + i, y);
     }
 }
 
@@ -549,7 +552,7 @@ __device__ __forceinline__ void copy_segment(const CSegArg &s, int lb, int nb) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             uint64_t i = base + (uint64_t)u * bd;
-            if (i < nv) vd[i] = vs[i];
+            if (i < nv) stp<false>(vd + i, ldp<false>(vs + i));
         }
     } else if (w == 4) {
         const uint32_t *vs = (const uint32_t *)(src + h);
