@@ -45,7 +45,7 @@ def finish(outs, n, dt, ref, step, what):
 @pytest.mark.parametrize("cfg", [dict(reduce_algo="direct"), dict(reduce_algo="ring"),
                                  dict(reduce_algo="ring", fused_hops=3)],
                          ids=["fold", "ring", "fused"])
-@pytest.mark.parametrize("R", [2, 5, 8])
+@pytest.mark.parametrize("R", [2, 5, 8, 17])
 @pytest.mark.parametrize("dt", DTS, ids=NAME.get)
 def test_reductions_where_no_two_buffers_share_alignment(dt, R, cfg):
     hc.set_config(copy_path="kernel", **cfg)
@@ -58,3 +58,26 @@ def test_reductions_where_no_two_buffers_share_alignment(dt, R, cfg):
         outs = outputs(R, n, dt, 2)
         hc.allreduce([shifted(xa[r], dt, (5 * r + 2) % 9) for r in range(R)], [o[1] for o in outs])
         finish(outs, n, dt, oracle.allreduce_new(xa, dt), 2, f"AR n={n}")
+
+
+@pytest.mark.parametrize("partials", [0, 1])
+@pytest.mark.parametrize("R", [6, 7, 9, 10, 16, 18, 24, 33])
+def test_fold_at_every_remainder_of_its_batches(R, partials):
+    """The fold keeps up to 8 ranks in registers and takes more in batches
+    of 8: R - 1 one batch exactly, one rank over, one short, and several."""
+    hc.set_config(reduce_algo="direct", bf16_partials=partials)
+    for dt in DTS:
+        hops = partials and dt == hc.BF16
+        for n in (5, 2049):
+            x = [W.random_values(NAME[dt], 920 + R, r, R * n) for r in range(R)]
+            outs = outputs(R, n, dt, 5)
+            hc.reduce_scatter([to_dev(a, dt) for a in x], [o[1] for o in outs])
+            ref = oracle.reduce_scatter_bf16_hops_new(x) if hops else oracle.reduce_scatter_new(x, dt)
+            finish(outs, n, dt, ref, 5, f"RS {NAME[dt]} n={n}")
+            xa = [W.random_values(NAME[dt], 930 + R, r, R * n + 1) for r in range(R)]
+            send = [to_dev(a, dt) for a in xa]
+            hc.allreduce(send)                        # in place
+            torch.cuda.synchronize()
+            ref = oracle.allreduce_bf16_hops_new(xa) if hops else oracle.allreduce_new(xa, dt)
+            for r in range(R):
+                assert_bitwise(from_dev(send[r], dt), ref[r], f"AR {NAME[dt]} n={R * n + 1} r={r}")
