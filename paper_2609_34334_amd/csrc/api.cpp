@@ -376,7 +376,12 @@ int auto_workgroups(const DeviceState &st, const hoccl_config_t &cfg, const Plan
         need(n, s.hops > 1 ? multihop_elems_per_thread(p.dtype)
                            : reduce_step_elems_per_thread(p.dtype, s.phase, p.bf16_partials));
     }
-    if (p.has_fold) need(p.fold.total, fold_elems_per_thread(p.dtype));
+    if (p.has_fold) {
+        // Whole workgroups for every chunk, so that no workgroup makes a
+        // second pass for a chunk's last vectors.
+        const unsigned long long v = (p.fold.c + fold_elems_per_thread(p.dtype) - 1) / fold_elems_per_thread(p.dtype);
+        passes = std::max(passes, (unsigned long long)p.R * ((v + threads - 1) / threads) * threads);
+    }
     if (cfg.copy_path == HOCCL_COPY_KERNEL)
         for (const CopyOp &c : p.copies) need((unsigned long long)c.bytes * p.R, copy_bytes_per_thread());
     return workgroups_for(st, cfg, passes, threads);

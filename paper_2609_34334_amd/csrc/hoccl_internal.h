@@ -178,6 +178,7 @@ template <int CAP>
 struct ReduceArgsT {
     RSegArg seg[CAP];
     int nseg;
+    uint32_t threads;  // per workgroup; set at the launch
 };
 using ReduceArgs = ReduceArgsT<kMaxReduceSegs>;
 
@@ -195,6 +196,7 @@ template <int CAP>
 struct MultiArgsT {
     MSegArg seg[CAP];
     int nseg;
+    uint32_t threads;  // per workgroup; set at the launch
 };
 using MultiArgs = MultiArgsT<kMaxMultiSegs>;
 
@@ -207,6 +209,7 @@ template <int CAP>
 struct CopyArgsT {
     CSegArg seg[CAP];
     int nseg;
+    uint32_t threads;  // per workgroup; set at the launch
 };
 using CopyArgs = CopyArgsT<kMaxCopySegs>;
 
@@ -219,6 +222,7 @@ struct FoldArgsT {
     int R;
     int write_all;
     int out_at_chunk;
+    uint32_t threads;  // per workgroup; set at the launch
 };
 using FoldArgs = FoldArgsT<kMaxRanks>;
 

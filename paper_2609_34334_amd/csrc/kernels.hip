@@ -164,25 +164,39 @@ __device__ __forceinline__ void stp(P *p, const P &x) {
     }
 }
 
-// Splits the blocks of a launch over `nseg` segments.  With at least one
-// block per segment, block b serves segment b % nseg (consecutive blocks go
-// to different segments, so every XCD streams every segment); otherwise each
-// block walks several segments.
-template <typename F>
+// Splits the blocks of a launch over `nseg` segments; f(seg, lb, nb) is block
+// lb of the nb blocks of segment seg.  With fewer blocks than segments each
+// block walks several segments.  Otherwise
+// * IN_TURN: block b serves segment b % nseg.  The ring's steps take this
+//   one: at 8 ranks chunk j then stays on XCD j from step to step (headline:
+//   266.6 us, against 269.5 with runs of blocks).
+// * else a run of consecutive blocks serves each segment, so that the launch
+//   sweeps the segments one after another and the blocks in flight read and
+//   write a few narrow windows of memory instead of nseg times as many.  The
+//   fold at R = 8, n = 3,145,728 (bf16) takes 74.3 us so and 78.6 in turn,
+//   at R = 7 71.9 and 84.1.  (Runs of blocks per XCD are no better than in
+//   turn: 78.9 and 77.7.)
+template <bool IN_TURN, typename F>
 __device__ __forceinline__ void for_each_segment(int nseg, F &&f) {
-    if ((int)gridDim.x >= nseg) {
-        int seg = (int)blockIdx.x % nseg;
-        int lb = (int)blockIdx.x / nseg;
-        int nb = ((int)gridDim.x - seg + nseg - 1) / nseg;
-        f(seg, lb, nb);
+    const int g = (int)gridDim.x, b = (int)blockIdx.x;
+    if (g >= nseg && IN_TURN) {
+        int seg = b % nseg;
+        f(seg, b / nseg, (g - seg + nseg - 1) / nseg);
+    } else if (g >= nseg) {
+        // The first `more` segments get q + 1 blocks, the others q.
+        const int q = g / nseg, more = g % nseg, c = b - more * (q + 1);
+        if (c < 0)
+            f(b / (q + 1), b % (q + 1), q + 1);
+        else
+            f(more + c / q, c % q, q);
     } else {
-        for (int seg = (int)blockIdx.x; seg < nseg; seg += (int)gridDim.x) f(seg, 0, 1);
+        for (int seg = b; seg < nseg; seg += g) f(seg, 0, 1);
     }
 }
 
 // ---- one ring step --------------------------------------------------------------
 template <class T0, class T1, class TO, int VE, int U, int NT>
-__device__ __forceinline__ void reduce_segment(const RSegArg &s, int lb, int nb) {
+__device__ __forceinline__ void reduce_segment(const RSegArg &s, int lb, int nb, uint32_t threads) {
     constexpr bool NT0 = NT & 1, NT1 = NT & 2, NTO = NT & 4;
     using S0 = typename T0::S;
     using S1 = typename T1::S;
@@ -204,7 +218,7 @@ __device__ __forceinline__ void reduce_segment(const RSegArg &s, int lb, int nb)
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
-    const uint64_t bd = blockDim.x;
+    const uint64_t bd = threads;
     const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
     const uint64_t stride = (uint64_t)nb * bd;
     for (uint64_t k = t; k < h; k += stride)
@@ -248,8 +262,8 @@ __device__ __forceinline__ const A &kernargs();
 template <class T0, class T1, class TO, int VE, int U, int NT, int CAP>
 __global__ void __launch_bounds__(1024) reduce_step_kernel(ReduceArgsT<CAP>) {
     const ReduceArgsT<CAP> &a = kernargs<ReduceArgsT<CAP>>();
-    for_each_segment(a.nseg, [&](int seg, int lb, int nb) {
-        reduce_segment<T0, T1, TO, VE, U, NT>(a.seg[seg], lb, nb);
+    for_each_segment<true>(a.nseg, [&](int seg, int lb, int nb) {
+        reduce_segment<T0, T1, TO, VE, U, NT>(a.seg[seg], lb, nb, a.threads);
     });
 }
 
@@ -263,7 +277,7 @@ __global__ void __launch_bounds__(1024) reduce_step_kernel(ReduceArgsT<CAP>) {
 // nloc is the same for every lane, so the guards on the unrolled
 // contribution loop are uniform branches.
 template <class T0, class T1, class TO, int VE, int U, int NT, int MAXL, bool RH>
-__device__ __forceinline__ void multihop_segment(const MSegArg &s, int lb, int nb) {
+__device__ __forceinline__ void multihop_segment(const MSegArg &s, int lb, int nb, uint32_t threads) {
     constexpr bool NT0 = NT & 1, NT1 = NT & 2, NTO = NT & 4;
     using S0 = typename T0::S;
     using S1 = typename T1::S;
@@ -294,7 +308,7 @@ __device__ __forceinline__ void multihop_segment(const MSegArg &s, int lb, int n
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
-    const uint64_t bd = blockDim.x;
+    const uint64_t bd = threads;
     const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
     const uint64_t stride = (uint64_t)nb * bd;
     auto scalar = [&](uint64_t k) {
@@ -371,8 +385,8 @@ __device__ __forceinline__ void multihop_segment(const MSegArg &s, int lb, int n
 template <class T0, class T1, class TO, int VE, int U, int NT, int MAXL, int CAP, bool RH>
 __global__ void __launch_bounds__(1024) multihop_kernel(MultiArgsT<CAP>) {
     const MultiArgsT<CAP> &a = kernargs<MultiArgsT<CAP>>();
-    for_each_segment(a.nseg, [&](int seg, int lb, int nb) __attribute__((always_inline)) {
-        multihop_segment<T0, T1, TO, VE, U, NT, MAXL, RH>(a.seg[seg], lb, nb);
+    for_each_segment<true>(a.nseg, [&](int seg, int lb, int nb) __attribute__((always_inline)) {
+        multihop_segment<T0, T1, TO, VE, U, NT, MAXL, RH>(a.seg[seg], lb, nb, a.threads);
     });
 }
 
@@ -415,7 +429,7 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
-    const uint64_t bd = blockDim.x;
+    const uint64_t bd = a.threads;
     const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
     const uint64_t stride = (uint64_t)nb * bd;
     auto scalar = [&](uint64_t k) {
@@ -543,18 +557,18 @@ __global__ void __launch_bounds__(1024) fold_kernel(FoldArgsT<CAP>) {
     // Forced inline: for_each_segment calls the body from two places, and
     // the eight-rank rounding fold was otherwise left an out-of-line call
     // with a scratch frame.
-    for_each_segment(a.R, [&](int j, int lb, int nb) __attribute__((always_inline)) {
+    for_each_segment<false>(a.R, [&](int j, int lb, int nb) __attribute__((always_inline)) {
         fold_chunk<T, VE, NR, RH>(a, j, lb, nb);
     });
 }
 
 // ---- CU copy ----------------------------------------------------------------------
 template <int U>
-__device__ __forceinline__ void copy_segment(const CSegArg &s, int lb, int nb) {
+__device__ __forceinline__ void copy_segment(const CSegArg &s, int lb, int nb, uint32_t threads) {
     const unsigned char *src = (const unsigned char *)s.src;
     unsigned char *dst = (unsigned char *)s.dst;
     const uint64_t n = s.bytes;
-    const uint64_t bd = blockDim.x;
+    const uint64_t bd = threads;
     const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
     const uint64_t stride = (uint64_t)nb * bd;
     // Widest unit for which source and destination share their misalignment.
@@ -595,8 +609,8 @@ constexpr int kCopyUnroll = HOCCL_COPY_UNROLL;
 template <int CAP>
 __global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP>) {
     const CopyArgsT<CAP> &a = kernargs<CopyArgsT<CAP>>();
-    for_each_segment(a.nseg, [&](int seg, int lb, int nb) {
-        copy_segment<kCopyUnroll>(a.seg[seg], lb, nb);
+    for_each_segment<true>(a.nseg, [&](int seg, int lb, int nb) {
+        copy_segment<kCopyUnroll>(a.seg[seg], lb, nb, a.threads);
     });
 }
 
@@ -606,9 +620,14 @@ __global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP>) {
 
 // hipLaunchKernel reports this launch's own status (hipGetLastError would
 // also return errors left behind by unrelated earlier calls).
+// Sets a.threads: a kernel that read its workgroup size from the hidden
+// arguments would start every wave with a vector load of it and the wait (the
+// headline ring, whose waves make one pass each, took 262.4 us so, and takes
+// 253.6 with the size among the arguments' scalar loads).
 template <typename Args>
-static hipError_t launch(const void *kernel, const Args &a, int wg, int threads, hipStream_t s) {
-    void *args[] = {const_cast<Args *>(&a)};
+static hipError_t launch(const void *kernel, Args a, int wg, int threads, hipStream_t s) {
+    a.threads = (uint32_t)threads;
+    void *args[] = {&a};
     return hipLaunchKernel(kernel, dim3((unsigned)wg), dim3((unsigned)threads), args, 0, s);
 }
 
