@@ -382,8 +382,6 @@ int auto_workgroups(const DeviceState &st, const hoccl_config_t &cfg, const Plan
         const unsigned long long v = (p.fold.c + fold_elems_per_thread(p.dtype) - 1) / fold_elems_per_thread(p.dtype);
         passes = std::max(passes, (unsigned long long)p.R * ((v + threads - 1) / threads) * threads);
     }
-    if (cfg.copy_path == HOCCL_COPY_KERNEL)
-        for (const CopyOp &c : p.copies) need((unsigned long long)c.bytes * p.R, copy_bytes_per_thread());
     return workgroups_for(st, cfg, passes, threads);
 }
 
@@ -626,32 +624,67 @@ hoccl_status_t run_engine_groups(DeviceState &st, const hoccl_config_t &cfg, con
     return r;
 }
 
+// An automatic copy launch has a workgroup for every tile, up to this many: a
+// row of tiles walked in several rounds is several windows of memory at once
+// (the gather of eight 48 MiB shards: 571 us with a workgroup per tile, 684
+// with 16384; an all-to-all(v) of 2.4 GB: 820 and 887).
+constexpr unsigned kMaxCopyWorkgroups = 1u << 20;
+
+// Consecutive copies of a level that read the same bytes (an all-gather's
+// shard, a broadcast's buffer) go into one segment of several destinations,
+// so that the source is read once for up to kMaxFan of them.  `wg` is raised
+// to the most workgroups of any launch here.
 hoccl_status_t run_copies_kernel(DeviceState &st, const hoccl_config_t &cfg, const Plan &p,
-                                 const Buffers &B, hipStream_t s, int wg, int threads) {
+                                 const Buffers &B, hipStream_t s, int &wg, int threads) {
     int maxlevel = 0;
     for (const CopyOp &c : p.copies) maxlevel = std::max(maxlevel, c.level);
+    CopyArgs one;
+    FanArgs fan;
+    auto flush = [&](auto &a, auto launch) -> hoccl_status_t {
+        if (a.nseg == 0) return HOCCL_OK;
+        const unsigned tiles = copy_tiles_of(a, threads, cfg.workgroups_per_step);
+        const int w = cfg.workgroups_per_step > 0 ? cfg.workgroups_per_step : (int)std::min(tiles, kMaxCopyWorkgroups);
+        TimingPair *tp;
+        TRY(timed_begin(st, cfg, s, &tp));
+        HIP_TRY(launch(a, w, threads, s));
+        TRY(timed_end(tp, s));
+        t_stats.copy_kernel_launches++;
+        wg = std::max(wg, w);
+        a.nseg = 0;
+        return HOCCL_OK;
+    };
     for (int lvl = 0; lvl <= maxlevel; ++lvl) {
-        CopyArgs a;
-        std::memset(&a, 0, sizeof a);
-        auto flush = [&]() -> hoccl_status_t {
-            if (a.nseg == 0) return HOCCL_OK;
-            TimingPair *tp;
-            TRY(timed_begin(st, cfg, s, &tp));
-            HIP_TRY(launch_copy(a, wg, threads, s));
-            TRY(timed_end(tp, s));
-            t_stats.copy_kernel_launches++;
-            std::memset(&a, 0, sizeof a);
-            return HOCCL_OK;
-        };
-        for (const CopyOp &c : p.copies) {
-            if (c.level != lvl) continue;
-            a.seg[a.nseg].src = resolve(c.src, B);
-            a.seg[a.nseg].dst = resolve(c.dst, B);
-            a.seg[a.nseg].bytes = c.bytes;
-            a.nseg++;
-            if (a.nseg == kMaxCopySegs) TRY(flush());
+        one.nseg = fan.nseg = 0;
+        for (size_t i = 0; i < p.copies.size();) {
+            const CopyOp &c = p.copies[i];
+            if (c.level != lvl) {
+                ++i;
+                continue;
+            }
+            const void *src = resolve(c.src, B);
+            size_t k = i + 1;
+            while (k < p.copies.size() && k < i + kMaxFan && p.copies[k].level == lvl &&
+                   p.copies[k].bytes == c.bytes && resolve(p.copies[k].src, B) == src)
+                ++k;
+            if (k == i + 1) {
+                CSegArgT<1> &g = one.seg[one.nseg++];
+                g.src = src;
+                g.dst[0] = resolve(c.dst, B);
+                g.bytes = c.bytes;
+                if (one.nseg == kMaxCopySegs) TRY(flush(one, launch_copy));
+            } else {
+                CSegArgT<kMaxFan> &g = fan.seg[fan.nseg++];
+                g.src = src;
+                g.bytes = c.bytes;
+                g.nd = (int)(k - i);
+                for (int q = 0; q < kMaxFan; ++q)
+                    g.dst[q] = q < g.nd ? resolve(p.copies[i + (size_t)q].dst, B) : nullptr;
+                if (fan.nseg == kMaxFanSegs) TRY(flush(fan, launch_fan));
+            }
+            i = k;
         }
-        TRY(flush());
+        TRY(flush(one, launch_copy));
+        TRY(flush(fan, launch_fan));
     }
     return HOCCL_OK;
 }
@@ -721,7 +754,7 @@ size_t auto_chunk_bytes(const DeviceState &st, const hoccl_config_t &cfg, hoccl_
 // Enqueues a plan's reductions and copies on `s` by the chosen copy path.
 hoccl_status_t enqueue_body(DeviceState &st, const hoccl_config_t &cfg, const Plan &p,
                             const Buffers &B, hipStream_t s, hoccl_copy_path_t path, int handshake,
-                            bool capturing, bool has_copies, int wg, int threads) {
+                            bool capturing, bool has_copies, int &wg, int threads) {
     if (has_copies && path == HOCCL_COPY_SDMA && !capturing && p.ngroups > 1 &&
         !p.reduce_steps.empty()) {
         TRY(run_engine_groups(st, cfg, p, B, s, wg, threads, handshake));
@@ -814,7 +847,7 @@ hoccl_status_t execute(Build build, bool in_place, const Buffers &B0, hipStream_
     }
 
     const int threads = cfg.threads_per_workgroup ? cfg.threads_per_workgroup : 256;
-    const int wg = auto_workgroups(st, cfg, p, threads);
+    int wg = auto_workgroups(st, cfg, p, threads);
     if (g_debug)
         std::fprintf(stderr, "hoccl: device %d stream %p workgroups %d copy_path %d%s plan %s\n",
                      st.device, (void *)s, wg, (int)path, capturing ? " (captured)" : "",

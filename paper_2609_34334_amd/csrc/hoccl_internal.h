@@ -200,18 +200,36 @@ struct MultiArgsT {
 };
 using MultiArgs = MultiArgsT<kMaxMultiSegs>;
 
-struct CSegArg {
+// A copy segment: one source and its nd destinations (at most ND).  `first`
+// is the segments' row of tiles (copy_tiles_of).
+template <int ND>
+struct CSegArgT {
     const void *src;
-    void *dst;
+    void *dst[ND];
     uint64_t bytes;
+    int nd;
 };
-template <int CAP>
+template <>
+struct CSegArgT<1> {
+    const void *src;
+    void *dst[1];
+    uint64_t bytes;
+    static constexpr int nd = 1;
+};
+template <int CAP, int ND>
 struct CopyArgsT {
-    CSegArg seg[CAP];
+    CSegArgT<ND> seg[CAP];
+    uint32_t first[CAP + 1];
+    uint32_t unroll;   // 16-byte vectors per thread of a tile
     int nseg;
     uint32_t threads;  // per workgroup; set at the launch
 };
-using CopyArgs = CopyArgsT<kMaxCopySegs>;
+using CopyArgs = CopyArgsT<kMaxCopySegs, 1>;
+// Copies that read the same bytes share a segment of up to kMaxFan
+// destinations: 32 segments take 3 KiB of arguments.
+constexpr int kMaxFan = 8;
+constexpr int kMaxFanSegs = 32;
+using FanArgs = CopyArgsT<kMaxFanSegs, kMaxFan>;
 
 template <int CAP>
 struct FoldArgsT {
@@ -246,14 +264,19 @@ hipError_t launch_fold(hoccl_dtype_t dt, const FoldArgs &a, int wg, int threads,
                        hipStream_t s, bool bf16_partials = false);
 hipError_t launch_multihop(hoccl_dtype_t dt, Phase ph, const MultiArgs &a, int wg, int threads,
                            hipStream_t s, bool bf16_partials = false);
+// Copies: copy_tiles_of lays the row of tiles (call it before the launch) for a
+// workgroup budget (0: none) and returns its length, the most workgroups the
+// launch can use.
+uint32_t copy_tiles_of(CopyArgs &a, int threads, int budget);
+uint32_t copy_tiles_of(FanArgs &a, int threads, int budget);
 hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s);
+hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s);
 
-// Work one thread does in one pass of each kernel's main loop (elements of
-// the collective's dtype, or bytes for the copy kernel).
+// Elements of the collective's dtype one thread covers in one pass of each
+// kernel's main loop.
 size_t reduce_step_elems_per_thread(hoccl_dtype_t dt, Phase ph, bool bf16_partials = false);
 size_t fold_elems_per_thread(hoccl_dtype_t dt);
 size_t multihop_elems_per_thread(hoccl_dtype_t dt);
-size_t copy_bytes_per_thread();
 hipError_t launch_handshake(const HandshakeArgs &a, hipStream_t s);
 
 // The static device scratch of hoccl_reduce_scatter_noalloc (scratch.hip):

@@ -6,8 +6,9 @@
 //   in1 is this rank's element.  bf16 partials are carried in fp32.
 // * fold_kernel        -- the direct variant: folds all R inputs of a chunk
 //   in the ring order in one pass (same result bit for bit, fewer bytes).
-// * copy_kernel        -- a CU copy of many independent (src, dst, bytes)
-//   segments; the comparator for the SDMA copy path.
+// * copy_kernel        -- a CU copy of many independent segments, each one
+//   source and one or several destinations; the comparator for the SDMA
+//   copy path.
 //
 // All three are HBM-bound streams (about one add per 8-12 bytes), so they
 // use 16-byte vector loads and stores, a grid-stride loop over each segment
@@ -79,20 +80,9 @@ struct Pack {
 #ifndef HOCCL_FOLD_NT_OUT
 #define HOCCL_FOLD_NT_OUT 1
 #endif
-// CU copy: 16-byte vectors in flight per thread and pass, and whether the
-// loads and the stores are non-temporal.  Measured on the copy workloads
-// (kernel copy path, back to back): 4 vectors with non-temporal stores
-// took the FSDP all-gather from 1.08 to 1.02 ms and a 64 MiB copy from 35
-// to 31 us against 2 plain vectors, and left the pipeline schedule, the
-// EP all-to-all(v) and a 2 GiB copy as they were; non-temporal loads as
-// well made the 2 GiB copy 6% faster but the all-gather and the pipeline
-// schedule about 20% slower (a shard is read by every rank's copy).
-#ifndef HOCCL_COPY_UNROLL
-#define HOCCL_COPY_UNROLL 4
-#endif
-#ifndef HOCCL_COPY_NT_IN
-#define HOCCL_COPY_NT_IN 0
-#endif
+// Whether the CU copy's stores are non-temporal.  Normal ones make the EP
+// all-to-all(v) 231 us instead of 217 and a 128 MiB send/recv 47.1 instead of
+// 45.9.
 #ifndef HOCCL_COPY_NT_OUT
 #define HOCCL_COPY_NT_OUT 1
 #endif
@@ -112,6 +102,8 @@ constexpr int kNtOnly = (HOCCL_NT_X ? 3 : 0) | (HOCCL_NT_FINAL ? 4 : 0);
 constexpr int kVeBf16Partial = 4;
 constexpr int kVeBf16Only = 8;
 constexpr int kVe32 = 4;
+constexpr int kDeepCopy = 4;  // vectors per thread of a deep copy tile (copy_tiles_of)
+constexpr int kWideFan = 4;   // destinations from which a copy is write-bound (launch_fan)
 
 // Byte-aligned vectors.  The compute units take a 16-byte global access at any
 // byte address (the HSA target runs with unaligned access enabled), so the
@@ -563,55 +555,77 @@ __global__ void __launch_bounds__(1024) fold_kernel(FoldArgsT<CAP>) {
 }
 
 // ---- CU copy ----------------------------------------------------------------------
-template <int U>
-__device__ __forceinline__ void copy_segment(const CSegArg &s, int lb, int nb, uint32_t threads) {
-    const unsigned char *src = (const unsigned char *)s.src;
-    unsigned char *dst = (unsigned char *)s.dst;
+// Tiles `at`, at + G, at + 2G, ... of one segment; a tile is U 16-byte
+// vectors per thread.  The vectors start where the first destination
+// reaches 16-byte alignment; a source or a further destination at another
+// phase is read or written misaligned.  The bytes before and after the
+// vectors, fewer than 31, go to the block of tile 0, one per lane.
+template <int U, int ND, bool NT_IN>
+__device__ __forceinline__ void copy_tiles(const CSegArgT<ND> &s, uint32_t at, uint32_t G, uint32_t bd) {
+    using V = Pack<uint32_t, 4>;  // HIP's uint4 is a union and defeats SROA
+    const char *src = (const char *)s.src;
     const uint64_t n = s.bytes;
-    const uint64_t bd = threads;
-    const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
-    const uint64_t stride = (uint64_t)nb * bd;
-    // Widest unit for which source and destination share their misalignment.
-    const uintptr_t x = (uintptr_t)src ^ (uintptr_t)dst;
-    const uint64_t w = (x & 15u) == 0 ? 16 : ((x & 3u) == 0 ? 4 : 1);
-    uint64_t h = w == 1 ? 0 : ((w - ((uintptr_t)src & (w - 1))) & (w - 1));
+    char *dst[ND];
+#pragma unroll
+    for (int q = 0; q < ND; ++q) dst[q] = (char *)s.dst[q < s.nd ? q : 0];
+    uint64_t h = (16u - ((uintptr_t)dst[0] & 15u)) & 15u;
     if (h > n) h = n;
-    const uint64_t nv = w == 1 ? 0 : (n - h) / w;
-    const uint64_t tail = h + nv * w;
-    for (uint64_t k = t; k < h; k += stride) dst[k] = src[k];
-    for (uint64_t k = (w == 1 ? 0 : tail) + t; k < n; k += stride) dst[k] = src[k];
-    if (w == 16) {
-        using V = Pack<uint32_t, 4>;  // HIP's uint4 is a union and defeats SROA
-        const V *vs = (const V *)(src + h);
-        V *vd = (V *)(dst + h);
-        uint64_t base = (uint64_t)lb * bd * U + threadIdx.x;
-        for (; base + (uint64_t)(U - 1) * bd < nv; base += stride * U) {
-            V v[U];
+    const uint64_t nv = (n - h) / 16;
+    const uint32_t t = threadIdx.x;
+    if (at == 0 && t < n - nv * 16) {
+        const uint64_t k = t < h ? t : nv * 16 + t;
+        const char x = src[k];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = ldp<HOCCL_COPY_NT_IN>(vs + base + (uint64_t)u * bd);
+        for (int q = 0; q < ND; ++q)
+            if (q < s.nd) dst[q][k] = x;
+    }
+    const V *vs = (const V *)(src + h);
+    const uint64_t tile = (uint64_t)bd * U, step = tile * G;
+    uint64_t base = tile * at;
+    for (; base + tile <= nv; base += step) {
+        V v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) stp<HOCCL_COPY_NT_OUT>(vd + base + (uint64_t)u * bd, v[u]);
+        for (int u = 0; u < U; ++u) v[u] = ldp<NT_IN>(vs + base + t + (uint64_t)u * bd);
+#pragma unroll
+        for (int q = 0; q < ND; ++q)
+            if (q < s.nd)
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    stp<HOCCL_COPY_NT_OUT>((V *)(dst[q] + h) + base + t + (uint64_t)u * bd, v[u]);
+    }
+    // At most one tile of this block reaches past the segment's end.
+    if (base >= nv) return;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t i = base + t + (uint64_t)u * bd;
+        if (i < nv) {
+            V v = ldp<NT_IN>(vs + i);
+#pragma unroll
+            for (int q = 0; q < ND; ++q)
+                if (q < s.nd) stp<HOCCL_COPY_NT_OUT>((V *)(dst[q] + h) + i, v);
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            uint64_t i = base + (uint64_t)u * bd;
-            if (i < nv) stp<false>(vd + i, ldp<false>(vs + i));
-        }
-    } else if (w == 4) {
-        const uint32_t *vs = (const uint32_t *)(src + h);
-        uint32_t *vd = (uint32_t *)(dst + h);
-        for (uint64_t i = t; i < nv; i += stride) vd[i] = vs[i];
     }
 }
 
-constexpr int kCopyUnroll = HOCCL_COPY_UNROLL;
-
-template <int CAP>
-__global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP>) {
-    const CopyArgsT<CAP> &a = kernargs<CopyArgsT<CAP>>();
-    for_each_segment<true>(a.nseg, [&](int seg, int lb, int nb) {
-        copy_segment<kCopyUnroll>(a.seg[seg], lb, nb, a.threads);
-    });
+// The tiles of all segments form one row (segment s has tiles first[s] up to
+// first[s + 1]); block b takes tiles b, b + G, b + 2G, ... of it.
+template <int CAP, int ND, int U, bool NT_IN>
+__global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP, ND>) {
+    const CopyArgsT<CAP, ND> &a = kernargs<CopyArgsT<CAP, ND>>();
+    const uint32_t G = gridDim.x;
+    for (uint32_t at = blockIdx.x; at < a.first[a.nseg];) {
+        int lo = 0, hi = a.nseg;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) / 2;
+            if (a.first[mid] <= at)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        const uint32_t b = a.first[lo], n = a.first[lo + 1] - b;
+        copy_tiles<U, ND, NT_IN>(a.seg[lo], at - b, G, a.threads);
+        at += ((n - 1 - (at - b)) / G + 1) * G;
+    }
 }
 
 }  // namespace
@@ -625,10 +639,10 @@ __global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP>) {
 // headline ring, whose waves make one pass each, took 262.4 us so, and takes
 // 253.6 with the size among the arguments' scalar loads).
 template <typename Args>
-static hipError_t launch(const void *kernel, Args a, int wg, int threads, hipStream_t s) {
+static hipError_t launch(const void *kernel, Args a, int wg, int threads, hipStream_t s, size_t lds = 0) {
     a.threads = (uint32_t)threads;
     void *args[] = {&a};
-    return hipLaunchKernel(kernel, dim3((unsigned)wg), dim3((unsigned)threads), args, 0, s);
+    return hipLaunchKernel(kernel, dim3((unsigned)wg), dim3((unsigned)threads), args, lds, s);
 }
 
 // The first a.nseg slots of `a` in an argument struct of CAP slots.
@@ -646,10 +660,14 @@ static MultiArgsT<CAP> fit(const MultiArgs &a) {
     b.nseg = a.nseg;
     return b;
 }
-template <int CAP>
-static CopyArgsT<CAP> fit(const CopyArgs &a) {
-    CopyArgsT<CAP> b{};
-    for (int k = 0; k < a.nseg; ++k) b.seg[k] = a.seg[k];
+template <int CAP, int C0, int ND>
+static CopyArgsT<CAP, ND> fit_copy(const CopyArgsT<C0, ND> &a) {
+    CopyArgsT<CAP, ND> b{};
+    for (int k = 0; k < a.nseg; ++k) {
+        b.seg[k] = a.seg[k];
+        b.first[k] = a.first[k];
+    }
+    b.first[a.nseg] = a.first[a.nseg];
     b.nseg = a.nseg;
     return b;
 }
@@ -817,7 +835,6 @@ size_t reduce_step_elems_per_thread(hoccl_dtype_t dt, Phase ph, bool bf16_partia
     return (size_t)kVe32 * HOCCL_RS_UNROLL_32;
 }
 size_t fold_elems_per_thread(hoccl_dtype_t dt) { return 16 / dtype_size(dt); }
-size_t copy_bytes_per_thread() { return 16 * kCopyUnroll; }
 
 // R up to 8 has a kernel of its own, whose arguments hold R ranks and whose
 // pointers all stay in scalar registers (R = 6, n = 1,398,103 bf16: 23.7 us,
@@ -852,11 +869,81 @@ hipError_t launch_fold(hoccl_dtype_t dt, const FoldArgs &a, int wg, int threads,
     return hipErrorInvalidValue;
 }
 
-// Copy launches of up to 8, 32 or 128 segments (200 bytes to 3 KiB of arguments).
+// The row of tiles of a launch, each `unroll` vectors per thread; returns its
+// length.
+template <int CAP, int ND>
+static uint32_t lay_tiles(CopyArgsT<CAP, ND> &a, int threads, int unroll) {
+    const uint64_t tile = (uint64_t)threads * 16 * (uint64_t)unroll;
+    uint32_t at = 0;
+    for (int k = 0; k < a.nseg; ++k) {
+        a.first[k] = at;
+        at += (uint32_t)((a.seg[k].bytes + tile - 1) / tile);
+    }
+    a.first[a.nseg] = at;
+    a.unroll = (uint32_t)unroll;
+    return at;
+}
+
+// Segments of one destination: tiles of one vector per thread, a workgroup
+// each.  Deeper tiles read and write a wider window at once: with 1, 2 and 4
+// vectors the EP all-to-all(v) takes 194, 195 and 213 us, one of 2.4 GB 752,
+// 791 and 855, a 1 GiB send/recv 346, 349 and 361 (eight 16 MiB messages 46
+// each).  Under a workgroup budget that leaves each several tiles, the bytes
+// in flight per wave set the rate instead (8 workgroups: 2.5 ms for 512 MiB
+// with 4 vectors, 4.2 with 2), so the tiles are deep.
+uint32_t copy_tiles_of(CopyArgs &a, int threads, int budget) {
+    const uint32_t tiles = lay_tiles(a, threads, 1);
+    return budget > 0 && (uint32_t)budget < tiles ? lay_tiles(a, threads, kDeepCopy) : tiles;
+}
+// Segments of several destinations: see launch_fan.
+uint32_t copy_tiles_of(FanArgs &a, int threads, int) {
+    int nd = 0;
+    for (int k = 0; k < a.nseg; ++k) nd = a.seg[k].nd > nd ? a.seg[k].nd : nd;
+    return lay_tiles(a, threads, nd >= kWideFan ? 1 : kDeepCopy);
+}
+
+// Copy launches of up to 8, 32 or 128 segments (250 bytes to 4 KiB of arguments).
+template <int U, bool NT>
+static hipError_t launch_copy_as(const CopyArgs &a, int wg, int threads, hipStream_t s) {
+    if (a.nseg <= 8) return launch((const void *)copy_kernel<8, 1, U, NT>, fit_copy<8>(a), wg, threads, s);
+    if (a.nseg <= 32) return launch((const void *)copy_kernel<32, 1, U, NT>, fit_copy<32>(a), wg, threads, s);
+    return launch((const void *)copy_kernel<kMaxCopySegs, 1, U, NT>, a, wg, threads, s);
+}
 hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s) {
-    if (a.nseg <= 8) return launch((const void *)copy_kernel<8>, fit<8>(a), wg, threads, s);
-    if (a.nseg <= 32) return launch((const void *)copy_kernel<32>, fit<32>(a), wg, threads, s);
-    return launch((const void *)copy_kernel<kMaxCopySegs>, a, wg, threads, s);
+    if (a.unroll != 1) return launch_copy_as<kDeepCopy, false>(a, wg, threads, s);
+    // Reading more than the 256 MB last-level cache holds, little of it can be
+    // there from an earlier write, and non-temporal loads are the faster ones:
+    // 204 us for the EP all-to-all(v) (608 MB) instead of 217, 747 for a 2 GiB
+    // copy instead of 772 (at 4 vectors per thread).  Where the data is in the
+    // cache they are slower: a pipeline schedule of 16 MiB messages, each read
+    // soon after it was written, would take 1234 us instead of 1119, a 64 MiB
+    // copy 32.8 instead of 28.3.
+    const uint64_t bytes = (uint64_t)a.first[a.nseg] * (uint64_t)threads * 16;
+    return bytes > ((uint64_t)256 << 20) ? launch_copy_as<1, true>(a, wg, threads, s)
+                                         : launch_copy_as<1, false>(a, wg, threads, s);
+}
+
+template <int U>
+static hipError_t launch_fan_u(const FanArgs &a, int wg, int threads, size_t lds, hipStream_t s) {
+    if (a.nseg <= 8)
+        return launch((const void *)copy_kernel<8, kMaxFan, U, false>, fit_copy<8>(a), wg, threads, s, lds);
+    return launch((const void *)copy_kernel<kMaxFanSegs, kMaxFan, U, false>, a, wg, threads, s, lds);
+}
+// Segments of several destinations.  From kWideFan destinations up the writes
+// dominate, and HBM takes them best when few workgroups are in flight, each
+// one vector deep per stream, so that the window they write to stays narrow:
+// the gather of eight 16 MiB shards takes 193 us (6.3 TB/s) with two
+// workgroups of 256 per CU and one vector, 239 with four vectors and as many
+// workgroups as fit, and took 347 as 64 copies that each read their source.
+// With two or three destinations there are too few bytes in flight then: two
+// 16 MiB shards take 21.7 us so and 16.2 with four vectors and no bound;
+// three 8 MiB shards 19.6 and 16.3; four 16 MiB shards 49.0 and 49.3.
+hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s) {
+    if (a.unroll != 1) return launch_fan_u<kDeepCopy>(a, wg, threads, 0, s);
+    // The kernel uses no LDS; asking for it bounds how many workgroups a CU
+    // holds (64 KiB of 160 KiB: two of 256 threads).
+    const size_t lds = threads <= 256 ? (size_t)threads << 8 : 0;
+    return launch_fan_u<1>(a, wg, threads, lds, s);
 }
 
 }  // namespace hoccl

@@ -81,3 +81,70 @@ def test_fold_at_every_remainder_of_its_batches(R, partials):
             ref = oracle.allreduce_bf16_hops_new(xa) if hops else oracle.allreduce_new(xa, dt)
             for r in range(R):
                 assert_bitwise(from_dev(send[r], dt), ref[r], f"AR {NAME[dt]} n={R * n + 1} r={r}")
+
+
+# Bytes around one vector, one lane's leftovers and a copy tile (256 threads
+# of one or of four 16-byte vectors).
+COPY_BYTES = [1, 15, 16, 33, 4095, 4097, 16_383, 16_385, 100_003]
+
+
+@pytest.mark.parametrize("wg", [0, 1, 7])
+@pytest.mark.parametrize("R", [2, 3, 4, 9, 17])
+def test_gathered_shards_share_their_source_reads(R, wg):
+    """The CU copy reads a shard once for up to eight destinations; every
+    rank's output starts at its own offset, and 9 and 17 ranks leave a
+    segment of a single destination."""
+    hc.set_config(copy_path="kernel", workgroups_per_step=wg)
+    for n in COPY_BYTES:
+        x = [W.random_bits(940 + R, r, n, 1) for r in range(R)]
+        ref = oracle.allgather_new(x, hc.UINT8)
+        outs = outputs(R, R * n, hc.UINT8, 5)
+        hc.allgather([shifted(x[r], hc.UINT8, (7 * r + 1) % 17) for r in range(R)], [o[1] for o in outs])
+        finish(outs, R * n, hc.UINT8, ref, 5, f"AG n={n}")
+        full = [to_dev(np.concatenate([x[r] if q == r else np.zeros(n, np.uint8) for q in range(R)]), hc.UINT8)
+                for r in range(R)]
+        hc.allgather([full[r][r * n:(r + 1) * n] for r in range(R)], full)          # in place
+        torch.cuda.synchronize()
+        for r in range(R):
+            assert_bitwise(from_dev(full[r], hc.UINT8), ref[r], f"AG in place n={n} r={r}")
+
+
+@pytest.mark.parametrize("wg", [0, 1, 5])
+@pytest.mark.parametrize("R", [2, 5, 12])
+def test_copies_of_unequal_ragged_segments(R, wg):
+    """All-to-all(v) by the CU copy: segments of every length around a tile,
+    empty ones among them, at odd offsets (144 of them take two launches),
+    with every workgroup walking several segments or none."""
+    hc.set_config(copy_path="kernel", workgroups_per_step=wg)
+    lens = [0, *COPY_BYTES]
+    counts = [lens[(3 * k + k // R) % len(lens)] for k in range(R * R)]
+    sd = [sum(counts[s * R:s * R + d]) + d for s in range(R) for d in range(R)]       # a byte apart
+    rd = [sum(counts[q * R + d] for q in range(s)) + 2 * s for s in range(R) for d in range(R)]
+    sizes = [sum(counts[s * R:(s + 1) * R]) + R for s in range(R)]
+    x = [W.random_bits(950 + R, r, sizes[r], 1) for r in range(R)]
+    rsizes = [sum(counts[s * R + d] for s in range(R)) + 2 * R for d in range(R)]
+    ref = [np.full(n, 0x5A, np.uint8) for n in rsizes]
+    oracle.alltoallv(x, counts, sd, ref, rd, hc.UINT8)
+    recv = [to_dev(np.full(n, 0x5A, np.uint8), hc.UINT8) for n in rsizes]
+    hc.alltoallv([to_dev(a, hc.UINT8) for a in x], counts, sd, recv, rd)
+    torch.cuda.synchronize()
+    for r in range(R):
+        assert_bitwise(from_dev(recv[r], hc.UINT8), ref[r], f"A2AV r={r}")
+
+
+def test_a_broadcast_reads_its_root_once_for_eight_ranks():
+    """Flows that read the same bytes share segments: a one-row
+    all-to-all(v), and one whose flows only partly coincide."""
+    hc.set_config(copy_path="kernel")
+    R, n = 11, 70_001
+    x = [W.random_bits(960, r, n, 2) for r in range(R)]
+    send = [to_dev(a, hc.BF16) for a in x]
+    for counts0 in ([0] + [n] * (R - 1), [0, n, n, n - 1, n, n, n, n, n, 5, 5]):
+        counts = counts0 + [0] * (R * (R - 1))
+        outs = outputs(R, n, hc.BF16, 2)
+        ref = [np.zeros(n, np.uint16) for _ in range(R)]
+        for o in outs:
+            o[1].zero_()
+        oracle.alltoallv(x, counts, [0] * (R * R), ref, [0] * (R * R), hc.BF16)
+        hc.alltoallv(send, counts, [0] * (R * R), [o[1] for o in outs], [0] * (R * R))
+        finish(outs, n, hc.BF16, ref, 2, f"broadcast {counts0[3]}")
