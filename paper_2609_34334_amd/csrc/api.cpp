@@ -367,21 +367,19 @@ int workgroups_for(const DeviceState &st, const hoccl_config_t &cfg, unsigned lo
 int auto_workgroups(const DeviceState &st, const hoccl_config_t &cfg, const Plan &p, int threads) {
     if (cfg.workgroups_per_step > 0) return cfg.workgroups_per_step;
     unsigned long long passes = 0;  // thread passes of the largest launch
-    auto need = [&](unsigned long long work, size_t per_thread) {
-        passes = std::max(passes, (work + per_thread - 1) / per_thread);
+    // Whole workgroups for every segment (ring chunk, fold chunk), so that no
+    // workgroup makes a second pass for a segment's last vectors.
+    auto need = [&](unsigned long long nseg, unsigned long long longest, size_t per_thread) {
+        const unsigned long long per_wg = (unsigned long long)per_thread * (unsigned long long)threads;
+        passes = std::max(passes, nseg * ((longest + per_wg - 1) / per_wg) * (unsigned long long)threads);
     };
     for (const ReduceStep &s : p.reduce_steps) {
-        unsigned long long n = 0;
-        for (const ReduceSeg &g : s.segs) n += g.n;
-        need(n, s.hops > 1 ? multihop_elems_per_thread(p.dtype)
-                           : reduce_step_elems_per_thread(p.dtype, s.phase, p.bf16_partials));
+        unsigned long long longest = 0;
+        for (const ReduceSeg &g : s.segs) longest = std::max(longest, (unsigned long long)g.n);
+        need(s.segs.size(), longest, s.hops > 1 ? multihop_elems_per_thread(p.dtype)
+                                                : reduce_step_elems_per_thread(p.dtype, s.phase, p.bf16_partials));
     }
-    if (p.has_fold) {
-        // Whole workgroups for every chunk, so that no workgroup makes a
-        // second pass for a chunk's last vectors.
-        const unsigned long long v = (p.fold.c + fold_elems_per_thread(p.dtype) - 1) / fold_elems_per_thread(p.dtype);
-        passes = std::max(passes, (unsigned long long)p.R * ((v + threads - 1) / threads) * threads);
-    }
+    if (p.has_fold) need((unsigned long long)p.R, p.fold.c, fold_elems_per_thread(p.dtype));
     return workgroups_for(st, cfg, passes, threads);
 }
 

@@ -156,6 +156,34 @@ __device__ __forceinline__ void stp(P *p, const P &x) {
     }
 }
 
+// Where a segment's vectors start: the first element at which `p` reaches a
+// cache line (128 bytes).  A wave's span of a line-aligned stream is whole
+// lines; from any other 16-byte boundary, every span shares its first and
+// last line with its neighbours', and the writes of both are parts of lines:
+// the gather of six shards of 3,333,333 bytes takes 21.2 us line-aligned and
+// 27.9 aligned to 16 bytes, an fp32 all-reduce of 1,500,007 elements at
+// R = 16 39.5 and 43.0, one of 2,100,001 bf16 at R = 12 23.9 and 25.8.
+constexpr uint32_t kLineBytes = 128;
+template <typename S>
+__device__ __forceinline__ uint64_t head_of(const S *p, uint64_t n) {
+    const uint64_t h = ((kLineBytes - ((uintptr_t)p & (kLineBytes - 1))) & (kLineBytes - 1)) / sizeof(S);
+    return h < n ? h : n;
+}
+
+// The elements before the vectors (h of them) and after (from `tail` to n),
+// one per lane: f(k).  They go to the last block of the segment, from its last
+// lane down: that block's vectors mostly end before its lanes do, so that its
+// idle waves take them (the all-reduce at R = 16 above: 34.5 us, against 39.5
+// with the first block's lanes).  Every wave runs the loop's test, on purpose:
+// the eight-rank fold, whose waves all start with it, takes 71 us at
+// n = 3,145,728 (bf16), and 77 with a uniform branch around the loop.
+template <typename F>
+__device__ __forceinline__ void for_each_edge(uint64_t h, uint64_t tail, uint64_t n, int lb, int nb, uint32_t bd,
+                                              F &&f) {
+    const uint64_t back = (uint64_t)(nb - 1 - lb) * bd + (bd - 1 - threadIdx.x);
+    for (uint64_t k = back; k < h + (n - tail); k += (uint64_t)nb * bd) f(k < h ? k : tail + (k - h));
+}
+
 // Splits the blocks of a launch over `nseg` segments; f(seg, lb, nb) is block
 // lb of the nb blocks of segment seg.  With fewer blocks than segments each
 // block walks several segments.  Otherwise
@@ -201,22 +229,17 @@ __device__ __forceinline__ void reduce_segment(const RSegArg &s, int lb, int nb,
     SO *out = (SO *)s.out;
     const uint64_t n = s.n;
 
-    // Elements before in1 reaches 16-byte alignment.  in0 and out mostly
-    // reach it at the same element; where they do not (the ring's last step
-    // into an output shard whose length is odd), their vectors are
+    // in0 and out mostly reach a line with in1; where they do not (the ring's
+    // last step into an output shard whose length is odd), their vectors are
     // misaligned.
-    uint64_t h = ((16u - ((uintptr_t)in1 & 15u)) & 15u) / sizeof(S1);
-    if (h > n) h = n;
+    const uint64_t h = head_of(in1, n);
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
     const uint64_t bd = threads;
-    const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
     const uint64_t stride = (uint64_t)nb * bd;
-    for (uint64_t k = t; k < h; k += stride)
-        out[k] = TO::narrow(T0::widen(in0[k]) + T1::widen(in1[k]));
-    for (uint64_t k = tail + t; k < n; k += stride)
-        out[k] = TO::narrow(T0::widen(in0[k]) + T1::widen(in1[k]));
+    for_each_edge(h, tail, n, lb, nb, threads,
+                  [&](uint64_t k) { out[k] = TO::narrow(T0::widen(in0[k]) + T1::widen(in1[k])); });
 
     const P0 *v0 = (const P0 *)(in0 + h);
     const P1 *v1 = (const P1 *)(in1 + h);
@@ -293,25 +316,26 @@ __device__ __forceinline__ void multihop_segment(const MSegArg &s, int lb, int n
 #pragma unroll
     for (int m = 0; m < MAXL; ++m) loc[m] = m < nl ? (const S1 *)s.loc[m] : (const S1 *)s.loc[0];
 
-    // Elements before the first contribution reaches 16-byte alignment; the
-    // operands that do not reach it there are read or written misaligned.
-    uint64_t h = ((16u - ((uintptr_t)loc[0] & 15u)) & 15u) / sizeof(S1);
-    if (h > n) h = n;
+    // The operands that do not reach a line with the first contribution are
+    // read or written misaligned.
+    const uint64_t h = head_of(loc[0], n);
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
     const uint64_t bd = threads;
-    const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
     const uint64_t stride = (uint64_t)nb * bd;
-    auto scalar = [&](uint64_t k) {
-        A acc = T0::widen(in0[k]);
+    for_each_edge(h, tail, n, lb, nb, threads, [&](uint64_t k) {
+        const S0 a = in0[k];
+        S1 b[MAXL];
 #pragma unroll
         for (int m = 0; m < MAXL; ++m)
-            if (m < nl) acc = add(acc, loc[m][k]);
+            if (m < nl) b[m] = loc[m][k];
+        A acc = T0::widen(a);
+#pragma unroll
+        for (int m = 0; m < MAXL; ++m)
+            if (m < nl) acc = add(acc, b[m]);
         out[k] = TO::narrow(acc);
-    };
-    for (uint64_t k = t; k < h; k += stride) scalar(k);
-    for (uint64_t k = tail + t; k < n; k += stride) scalar(k);
+    });
 
     const P0 *v0 = (const P0 *)(in0 + h);
     const P1 *vl[MAXL];
@@ -413,25 +437,31 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
     const int nout = a.write_all ? R : 1;
     auto dst = [&](int q) -> S * { return (S *)a.out[a.write_all ? q : j] + oe; };
 
-    // Elements before the first operand reaches 16-byte alignment.  A chunk
-    // of odd length leaves the inputs' phase and the output shard's apart: the
-    // reads are kept aligned (R streams) and the one write is misaligned.
-    uint64_t h = ((16u - ((uintptr_t)src(0) & 15u)) & 15u) / sizeof(S);
-    if (h > n) h = n;
+    // A chunk of odd length leaves the inputs' phase and the output shard's
+    // apart: the reads are kept aligned (R streams) and the one write is
+    // misaligned (R = 6, n = 1,398,103 bf16: 19.8 us, 21.2 the other way).
+    const uint64_t h = head_of(src(0), n);
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
 
     const uint64_t bd = a.threads;
     const uint64_t t = (uint64_t)lb * bd + threadIdx.x;
     const uint64_t stride = (uint64_t)nb * bd;
-    auto scalar = [&](uint64_t k) {
+    // The ranks' loads go out in batches here, too, not each after the last.
+    for_each_edge(h, tail, n, lb, nb, a.threads, [&](uint64_t k) __attribute__((always_inline)) {
+        constexpr int B = NR > 0 ? NR : 8;
         A acc = T::widen(src(0)[k]);
-        for (int q = 1; q < R; ++q) acc = add(acc, src(q)[k]);
-        S y = T::narrow(acc);
+        for (int q0 = 1; q0 < R; q0 += B) {
+            S x[B];
+#pragma unroll
+            for (int q = 0; q < B; ++q) x[q] = src(q0 + q < R ? q0 + q : 0)[k];
+#pragma unroll
+            for (int q = 0; q < B; ++q)
+                if (q0 + q < R) acc = add(acc, x[q]);
+        }
+        const S y = T::narrow(acc);
         for (int q = 0; q < nout; ++q) dst(q)[k] = y;
-    };
-    for (uint64_t k = t; k < h; k += stride) scalar(k);
-    for (uint64_t k = tail + t; k < n; k += stride) scalar(k);
+    });
 
     constexpr bool NT = HOCCL_FOLD_NT;
     constexpr bool NTO = HOCCL_FOLD_NT_OUT;
@@ -555,30 +585,30 @@ __global__ void __launch_bounds__(1024) fold_kernel(FoldArgsT<CAP>) {
 }
 
 // ---- CU copy ----------------------------------------------------------------------
-// Tiles `at`, at + G, at + 2G, ... of one segment; a tile is U 16-byte
-// vectors per thread.  The vectors start where the first destination
-// reaches 16-byte alignment; a source or a further destination at another
-// phase is read or written misaligned.  The bytes before and after the
-// vectors, fewer than 31, go to the block of tile 0, one per lane.
+// Tiles `at`, at + G, at + 2G, ... of one segment, up to its last one or not
+// (`last`); a tile is U 16-byte vectors per thread.  The vectors start where the first destination
+// reaches a line; a source or a further destination at another phase is read
+// or written misaligned.  The bytes before and after the vectors, fewer than
+// 144, go to the block of the last tile.
 template <int U, int ND, bool NT_IN>
-__device__ __forceinline__ void copy_tiles(const CSegArgT<ND> &s, uint32_t at, uint32_t G, uint32_t bd) {
+__device__ __forceinline__ void copy_tiles(const CSegArgT<ND> &s, uint32_t at, bool last, uint32_t G,
+                                           uint32_t bd) {
     using V = Pack<uint32_t, 4>;  // HIP's uint4 is a union and defeats SROA
     const char *src = (const char *)s.src;
     const uint64_t n = s.bytes;
     char *dst[ND];
 #pragma unroll
     for (int q = 0; q < ND; ++q) dst[q] = (char *)s.dst[q < s.nd ? q : 0];
-    uint64_t h = (16u - ((uintptr_t)dst[0] & 15u)) & 15u;
-    if (h > n) h = n;
+    const uint64_t h = head_of(dst[0], n);
     const uint64_t nv = (n - h) / 16;
     const uint32_t t = threadIdx.x;
-    if (at == 0 && t < n - nv * 16) {
-        const uint64_t k = t < h ? t : nv * 16 + t;
-        const char x = src[k];
+    if (last)
+        for_each_edge(h, h + nv * 16, n, 0, 1, bd, [&](uint64_t k) {
+            const char x = src[k];
 #pragma unroll
-        for (int q = 0; q < ND; ++q)
-            if (q < s.nd) dst[q][k] = x;
-    }
+            for (int q = 0; q < ND; ++q)
+                if (q < s.nd) dst[q][k] = x;
+        });
     const V *vs = (const V *)(src + h);
     const uint64_t tile = (uint64_t)bd * U, step = tile * G;
     uint64_t base = tile * at;
@@ -622,9 +652,9 @@ __global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP, ND>) {
             else
                 hi = mid;
         }
-        const uint32_t b = a.first[lo], n = a.first[lo + 1] - b;
-        copy_tiles<U, ND, NT_IN>(a.seg[lo], at - b, G, a.threads);
-        at += ((n - 1 - (at - b)) / G + 1) * G;
+        const uint32_t b = a.first[lo], left = a.first[lo + 1] - 1 - at, jump = left / G * G;
+        copy_tiles<U, ND, NT_IN>(a.seg[lo], at - b, jump == left, G, a.threads);
+        at += jump + G;
     }
 }
 

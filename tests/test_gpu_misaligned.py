@@ -148,3 +148,30 @@ def test_a_broadcast_reads_its_root_once_for_eight_ranks():
         oracle.alltoallv(x, counts, [0] * (R * R), ref, [0] * (R * R), hc.BF16)
         hc.alltoallv(send, counts, [0] * (R * R), [o[1] for o in outs], [0] * (R * R))
         finish(outs, n, hc.BF16, ref, 2, f"broadcast {counts0[3]}")
+
+
+@pytest.mark.parametrize("lead", [1, 31, 33, 63, 64, 127])
+@pytest.mark.parametrize("threads, wg", [(64, 0), (64, 3), (256, 0)])
+def test_heads_up_to_a_cache_line(lead, threads, wg):
+    """Vectors start where a buffer reaches a 128-byte line: heads from one
+    element to all but one of a line, with segments that end inside the head
+    and just after it, and more left-over elements than a workgroup has
+    lanes."""
+    for n in (5, 64, 65, 131, 2113):
+        for R, cfg in ((3, dict(reduce_algo="direct")), (9, dict(reduce_algo="direct")),
+                       (4, dict(reduce_algo="ring")), (4, dict(reduce_algo="ring", fused_hops=2))):
+            hc.set_config(copy_path="kernel", threads_per_workgroup=threads, workgroups_per_step=wg,
+                          **{"fused_hops": 1, **cfg})
+            for dt in DTS:
+                x = [W.random_values(NAME[dt], 970 + R, r, R * n) for r in range(R)]
+                outs = outputs(R, n, dt, 4)
+                hc.reduce_scatter([shifted(a, dt, lead) for a in x], [o[1] for o in outs])
+                finish(outs, n, dt, oracle.reduce_scatter_new(x, dt), 4, f"RS {cfg} n={n}")
+        for R in (2, 5):
+            x = [W.random_bits(980 + R, r, n, 1) for r in range(R)]
+            pads = [padded(R * n, hc.UINT8, lead=lead + r) for r in range(R)]
+            hc.allgather([to_dev(a, hc.UINT8) for a in x], [w for _, w in pads])
+            torch.cuda.synchronize()
+            for r, (full, win) in enumerate(pads):
+                check_canaries(full, lead + r, R * n, hc.UINT8)
+                assert_bitwise(from_dev(win, hc.UINT8), oracle.allgather_new(x, hc.UINT8)[r], f"AG n={n} r={r}")
