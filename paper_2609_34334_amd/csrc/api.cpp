@@ -472,6 +472,7 @@ hoccl_status_t run_reductions(DeviceState &st, const hoccl_config_t &cfg, const 
                 a.seg[k].n = g.n;
             }
             a.nseg = ns;
+            a.back = step.back;
             TimingPair *tp;
             TRY(timed_begin(st, cfg, s, &tp));
             HIP_TRY(launch_multihop(p.dtype, step.phase, a, wg, threads, s, p.bf16_partials));
@@ -490,6 +491,7 @@ hoccl_status_t run_reductions(DeviceState &st, const hoccl_config_t &cfg, const 
                 a.seg[k].n = g.n;
             }
             a.nseg = ns;
+            a.back = step.back;
             TimingPair *tp;
             TRY(timed_begin(st, cfg, s, &tp));
             HIP_TRY(launch_reduce_step(p.dtype, step.phase, a, wg, threads, s, p.bf16_partials));

@@ -57,8 +57,23 @@ struct ReduceStep {
     int group = 0;
     int step = 0;   // the first ring hop the launch performs
     int hops = 1;
+    // The launch walks its segments from their ends.  Every other step of a
+    // ring does, so that a step first reads the partials that the one before
+    // wrote last and the caches still hold (kBackBytes).
+    bool back = false;
     std::vector<ReduceSeg> segs;
 };
+
+// Ring steps alternate their direction where a step's partials take at least
+// this much and a partial is read by more than one launch.  R = 8, n =
+// 3,145,728 (100 MB of fp32 partials): 241 us alternating, 252 all forward;
+// fp32 308 and 319; bf16 partials 159 and 171; R = 12, n = 1,000,000 (48 MB):
+// 199 and 234; R = 32, n = 300,000 (38 MB): 446 and 513; R = 16, n = 300,001
+// (19 MB): 128 and 130.  Less is in the 32 MB of L2 whichever way (R = 10, n
+// = 400,000, 16 MB: 65.7 and 66.1; R = 12, int32, n = 200,000, 10 MB: 81.9 and
+// 80.2).  Two launches gain nothing (R = 7 in hops of 4: 53.2 and 53.4; R =
+// 5, fp32, in hops of 2: 83.2 and 80.5).
+constexpr size_t kBackBytes = (size_t)16 << 20;
 
 // Ring hops one fused launch may fold (contributions per segment).
 constexpr int kMaxHops = 8;
@@ -179,6 +194,7 @@ struct ReduceArgsT {
     RSegArg seg[CAP];
     int nseg;
     uint32_t threads;  // per workgroup; set at the launch
+    int back;          // ReduceStep::back
 };
 using ReduceArgs = ReduceArgsT<kMaxReduceSegs>;
 
@@ -197,6 +213,7 @@ struct MultiArgsT {
     MSegArg seg[CAP];
     int nseg;
     uint32_t threads;  // per workgroup; set at the launch
+    int back;          // ReduceStep::back
 };
 using MultiArgs = MultiArgsT<kMaxMultiSegs>;
 

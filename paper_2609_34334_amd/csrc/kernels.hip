@@ -184,6 +184,9 @@ __device__ __forceinline__ void for_each_edge(uint64_t h, uint64_t tail, uint64_
     for (uint64_t k = back; k < h + (n - tail); k += (uint64_t)nb * bd) f(k < h ? k : tail + (k - h));
 }
 
+// Workgroups are dealt to the GPU's eight XCDs, each with an L2, in turn.
+constexpr int kXcds = 8;
+
 // Splits the blocks of a launch over `nseg` segments; f(seg, lb, nb) is block
 // lb of the nb blocks of segment seg.  With fewer blocks than segments each
 // block walks several segments.  Otherwise
@@ -196,9 +199,16 @@ __device__ __forceinline__ void for_each_edge(uint64_t h, uint64_t tail, uint64_
 //   fold at R = 8, n = 3,145,728 (bf16) takes 74.3 us so and 78.6 in turn,
 //   at R = 7 71.9 and 84.1.  (Runs of blocks per XCD are no better than in
 //   turn: 78.9 and 77.7.)
+// `back` turns the blocks' order round, in groups of kXcds so that every part
+// of a segment stays on its XCD (ReduceStep::back says where and why).
 template <bool IN_TURN, typename F>
-__device__ __forceinline__ void for_each_segment(int nseg, F &&f) {
-    const int g = (int)gridDim.x, b = (int)blockIdx.x;
+__device__ __forceinline__ void for_each_segment(int nseg, bool back, F &&f) {
+    const int g = (int)gridDim.x;
+    int b = (int)blockIdx.x;
+    if (back) {
+        const int whole = g & ~(kXcds - 1);  // a rest of the grid keeps its place
+        if (b < whole) b = whole - kXcds - (b & ~(kXcds - 1)) + (b & (kXcds - 1));
+    }
     if (g >= nseg && IN_TURN) {
         int seg = b % nseg;
         f(seg, b / nseg, (g - seg + nseg - 1) / nseg);
@@ -277,7 +287,7 @@ __device__ __forceinline__ const A &kernargs();
 template <class T0, class T1, class TO, int VE, int U, int NT, int CAP>
 __global__ void __launch_bounds__(1024) reduce_step_kernel(ReduceArgsT<CAP>) {
     const ReduceArgsT<CAP> &a = kernargs<ReduceArgsT<CAP>>();
-    for_each_segment<true>(a.nseg, [&](int seg, int lb, int nb) {
+    for_each_segment<true>(a.nseg, a.back, [&](int seg, int lb, int nb) {
         reduce_segment<T0, T1, TO, VE, U, NT>(a.seg[seg], lb, nb, a.threads);
     });
 }
@@ -401,7 +411,7 @@ __device__ __forceinline__ void multihop_segment(const MSegArg &s, int lb, int n
 template <class T0, class T1, class TO, int VE, int U, int NT, int MAXL, int CAP, bool RH>
 __global__ void __launch_bounds__(1024) multihop_kernel(MultiArgsT<CAP>) {
     const MultiArgsT<CAP> &a = kernargs<MultiArgsT<CAP>>();
-    for_each_segment<true>(a.nseg, [&](int seg, int lb, int nb) __attribute__((always_inline)) {
+    for_each_segment<true>(a.nseg, a.back, [&](int seg, int lb, int nb) __attribute__((always_inline)) {
         multihop_segment<T0, T1, TO, VE, U, NT, MAXL, RH>(a.seg[seg], lb, nb, a.threads);
     });
 }
@@ -579,7 +589,7 @@ __global__ void __launch_bounds__(1024) fold_kernel(FoldArgsT<CAP>) {
     // Forced inline: for_each_segment calls the body from two places, and
     // the eight-rank rounding fold was otherwise left an out-of-line call
     // with a scratch frame.
-    for_each_segment<false>(a.R, [&](int j, int lb, int nb) __attribute__((always_inline)) {
+    for_each_segment<false>(a.R, false, [&](int j, int lb, int nb) __attribute__((always_inline)) {
         fold_chunk<T, VE, NR, RH>(a, j, lb, nb);
     });
 }
@@ -681,6 +691,7 @@ static ReduceArgsT<CAP> fit(const ReduceArgs &a) {
     ReduceArgsT<CAP> b{};
     for (int k = 0; k < a.nseg; ++k) b.seg[k] = a.seg[k];
     b.nseg = a.nseg;
+    b.back = a.back;
     return b;
 }
 template <int CAP>
@@ -688,6 +699,7 @@ static MultiArgsT<CAP> fit(const MultiArgs &a) {
     MultiArgsT<CAP> b{};
     for (int k = 0; k < a.nseg; ++k) b.seg[k] = a.seg[k];
     b.nseg = a.nseg;
+    b.back = a.back;
     return b;
 }
 template <int CAP, int C0, int ND>

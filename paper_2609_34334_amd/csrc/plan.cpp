@@ -136,6 +136,7 @@ static void ring_reduce(Plan &p, hoccl_dtype_t dt, int R, size_t stride,
         st.step = s0;
         st.hops = s1 - s0;
         st.phase = first ? (last ? PH_ONLY : PH_FIRST) : (last ? PH_LAST : PH_MIDDLE);
+        size_t partial_bytes = 0;
         // Segments in chunk order: launch block b serves segment b mod R
         // and lands on XCD b mod 8, so at R = 8 chunk j's partial is
         // written and read again by the same XCD at every step.
@@ -148,6 +149,7 @@ static void ring_reduce(Plan &p, hoccl_dtype_t dt, int R, size_t stride,
             size_t e = (size_t)j * stride + g0;  // first element (input index space)
             ReduceSeg sg;
             sg.n = n;
+            partial_bytes += n * as;
             sg.in1 = ref(BUF_SEND, r, e * es);
             for (int h = s0 + 1; h < s1; ++h) sg.more.push_back(ref(BUF_SEND, mod(j + h + 2, R), e * es));
             if (first)
@@ -164,6 +166,7 @@ static void ring_reduce(Plan &p, hoccl_dtype_t dt, int R, size_t stride,
                            (unsigned long long)n * es * sg.more.size();
             st.segs.push_back(std::move(sg));
         }
+        st.back = R - 1 > 2 * H && (s0 / H) % 2 == 1 && partial_bytes >= kBackBytes;
         if (!st.segs.empty()) p.reduce_steps.push_back(std::move(st));
     }
 }

@@ -175,3 +175,17 @@ def test_heads_up_to_a_cache_line(lead, threads, wg):
             for r, (full, win) in enumerate(pads):
                 check_canaries(full, lead + r, R * n, hc.UINT8)
                 assert_bitwise(from_dev(win, hc.UINT8), oracle.allgather_new(x, hc.UINT8)[r], f"AG n={n} r={r}")
+
+
+@pytest.mark.parametrize("wg", [0, 3, 13, 24])
+@pytest.mark.parametrize("R, hops, n", [(5, 1, 900_001), (9, 2, 500_003)])
+def test_ring_steps_that_alternate_their_direction(R, hops, n, wg):
+    """Partials of 16 MiB and more turn every other step's block order round:
+    with a workgroup per tile, fewer workgroups than segments, and grids that
+    do and do not divide by the XCDs."""
+    hc.set_config(reduce_algo="ring", fused_hops=hops, workgroups_per_step=wg)
+    for dt in (hc.INT32, hc.BF16):
+        x = [W.random_values(NAME[dt], 990 + R, r, R * n) for r in range(R)]
+        outs = outputs(R, n, dt, 5)
+        hc.reduce_scatter([to_dev(a, dt) for a in x], [o[1] for o in outs])
+        finish(outs, n, dt, oracle.reduce_scatter_new(x, dt), 5, f"RS {NAME[dt]} wg={wg}")
