@@ -883,9 +883,21 @@ size_t fold_elems_per_thread(hoccl_dtype_t dt) { return 16 / dtype_size(dt); }
 // against 27.3 by the kernel for any R; R = 5, n = 5,242,880 bf16: 54 against
 // 61).  More ranks would need more than the 100 or so scalar registers a
 // wave has.
+//
+// An all-reduce of three or more ranks writes as much as it reads, and HBM
+// takes that better when fewer workgroups are in flight and the windows they
+// write stay narrow: asking for LDS that the kernel does not use bounds them
+// to 1024 threads per CU (40 KiB of 160 for 256).  fp32, R = 3, n = 12,582,912:
+// 49.8 us so, 51.9 unbounded; bf16, R = 4, same n: 33.6 and 34.7; fp32, R = 4:
+// 65.4 and 67.2; bf16, R = 5, n = 5,000,011, bf16 partials: 17.5 and 18.3;
+// bf16, R = 8: 142 either way (its registers leave five workgroups).  With one
+// write for R reads, or two ranks, there would be too few bytes in flight:
+// reduce-scatter, R = 4, n = 6,000,000 bf16 43.1 so and 38.2 unbounded;
+// all-reduce, R = 2, n = 25,165,824 bf16 35.0 and 32.6.
 template <class T, int VE, int NR, bool RH>
 static hipError_t launch_fold_r(const FoldArgs &a, int wg, int threads, hipStream_t s) {
-    return launch((const void *)fold_kernel<T, VE, NR, NR, RH>, fit<NR>(a), wg, threads, s);
+    const size_t lds = a.write_all && NR >= 3 && threads <= 256 ? (size_t)threads * 160 : 0;
+    return launch((const void *)fold_kernel<T, VE, NR, NR, RH>, fit<NR>(a), wg, threads, s, lds);
 }
 
 template <class T, int VE, bool RH = false>
