@@ -1724,7 +1724,7 @@ def copy_kernel_workload(hc, W):
     HIP events per call): a 2 GiB and a 64 MiB copy, the FSDP all-gather,
     the PP schedule (32 rounds of seven 16 MiB hops) and the EP
     all-to-all(v), all on copy path `kernel`.  Run once per build of the
-    kernel's knobs (HOCCL_COPY_UNROLL, HOCCL_COPY_NT_IN, HOCCL_COPY_NT_OUT)
+    kernel's knob (HOCCL_COPY_NT_OUT)
     to compare them."""
     import torch
     res = {}

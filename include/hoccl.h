@@ -82,8 +82,8 @@
  *   all-gather      send[r] == recv[r] + r * sendcount elements;
  *   reduce-scatter  recv[r] == send[r] + r * recvcount elements.
  *   All other collectives are out-of-place only.
- * Alignment.  Any element-aligned pointer is accepted; 16-byte aligned
- *   buffers take the vectorised fast path.
+ * Alignment.  Any element-aligned pointer is accepted and takes the vector
+ *   path; buffers that start on a 128-byte line are the fastest.
  */
 #ifndef HOCCL_H
 #define HOCCL_H
