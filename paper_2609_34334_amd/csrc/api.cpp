@@ -364,7 +364,10 @@ int workgroups_for(const DeviceState &st, const hoccl_config_t &cfg, unsigned lo
     return (int)std::min(hi, std::max(lo, wg));
 }
 
+// Workgroups of a plan's reduction launches: 0 where it has none (a launch of
+// the copy kernel counts its own).
 int auto_workgroups(const DeviceState &st, const hoccl_config_t &cfg, const Plan &p, int threads) {
+    if (p.reduce_steps.empty() && !p.has_fold) return 0;
     if (cfg.workgroups_per_step > 0) return cfg.workgroups_per_step;
     unsigned long long passes = 0;  // thread passes of the largest launch
     // Whole workgroups for every segment (ring chunk, fold chunk), so that no
@@ -848,10 +851,6 @@ hoccl_status_t execute(Build build, bool in_place, const Buffers &B0, hipStream_
 
     const int threads = cfg.threads_per_workgroup ? cfg.threads_per_workgroup : 256;
     int wg = auto_workgroups(st, cfg, p, threads);
-    if (g_debug)
-        std::fprintf(stderr, "hoccl: device %d stream %p workgroups %d copy_path %d%s plan %s\n",
-                     st.device, (void *)s, wg, (int)path, capturing ? " (captured)" : "",
-                     plan_to_json(p).c_str());
     if (!p.copies.empty() && path == HOCCL_COPY_SDMA && !st.proxy) {
         // Asked for explicitly: never fall back silently.
         set_err("%s", st.proxy_why.c_str());
@@ -913,6 +912,10 @@ hoccl_status_t execute(Build build, bool in_place, const Buffers &B0, hipStream_
     // workspace user on another stream must wait for them.
     hoccl_status_t body = enqueue_body(st, cfg, p, B, s, path, handshake, capturing, has_copies, wg,
                                        threads);
+    if (g_debug)
+        std::fprintf(stderr, "hoccl: device %d stream %p workgroups %d copy_path %d%s plan %s\n",
+                     st.device, (void *)s, wg, (int)path, capturing ? " (captured)" : "",
+                     plan_to_json(p).c_str());
     if (p.ws_bytes && !capturing && !noalloc) {
         hipError_t e = hipEventRecord(st.ws_event, s);
         if (e == hipSuccess) {
