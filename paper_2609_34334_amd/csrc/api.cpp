@@ -386,6 +386,22 @@ int auto_workgroups(const DeviceState &st, const hoccl_config_t &cfg, const Plan
     return workgroups_for(st, cfg, passes, threads);
 }
 
+// Whether kernels on `s` may use every CU: a stream may have been made with a
+// mask that leaves some out.
+bool whole_chip(const DeviceState &st, hipStream_t s) {
+    uint32_t mask[16] = {};
+    if (hipExtStreamGetCUMask(s, 16, mask) != hipSuccess) return false;
+    int cus = 0;
+    for (uint32_t m : mask) cus += __builtin_popcount(m);
+    return cus >= st.num_cus;
+}
+
+// `want` bytes of LDS (fold_lds, copy_lds), or none where the bound they set
+// would cost: under a workgroup budget and on a part of the CUs.
+size_t lds_for(const DeviceState &st, const hoccl_config_t &cfg, hipStream_t s, size_t want) {
+    return want > 0 && cfg.workgroups_per_step == 0 && whole_chip(st, s) ? want : 0;
+}
+
 // Launches timed between two reads of hoccl_get_kernel_times; later ones go
 // untimed, so a caller that never reads does not grow the event pool
 // without bound.
@@ -528,7 +544,8 @@ hoccl_status_t run_reductions(DeviceState &st, const hoccl_config_t &cfg, const 
         a.out_at_chunk = p.fold.out_at_chunk ? 1 : 0;
         TimingPair *tp;
         TRY(timed_begin(st, cfg, s, &tp));
-        HIP_TRY(launch_fold(p.dtype, a, wg, threads, s, p.bf16_partials));
+        HIP_TRY(launch_fold(p.dtype, a, wg, threads, s, p.bf16_partials,
+                            lds_for(st, cfg, s, fold_lds(p.dtype, a, threads))));
         TRY(timed_end(tp, s));
         t_stats.reduce_launches++;
     }
@@ -649,7 +666,7 @@ hoccl_status_t run_copies_kernel(DeviceState &st, const hoccl_config_t &cfg, con
         const int w = cfg.workgroups_per_step > 0 ? cfg.workgroups_per_step : (int)std::min(tiles, kMaxCopyWorkgroups);
         TimingPair *tp;
         TRY(timed_begin(st, cfg, s, &tp));
-        HIP_TRY(launch(a, w, threads, s));
+        HIP_TRY(launch(a, w, threads, s, lds_for(st, cfg, s, copy_lds(a, w, threads))));
         TRY(timed_end(tp, s));
         t_stats.copy_kernel_launches++;
         wg = std::max(wg, w);

@@ -278,7 +278,7 @@ struct HandshakeArgs {
 hipError_t launch_reduce_step(hoccl_dtype_t dt, Phase ph, const ReduceArgs &a, int wg,
                               int threads, hipStream_t s, bool bf16_partials = false);
 hipError_t launch_fold(hoccl_dtype_t dt, const FoldArgs &a, int wg, int threads,
-                       hipStream_t s, bool bf16_partials = false);
+                       hipStream_t s, bool bf16_partials = false, size_t lds = 0);
 hipError_t launch_multihop(hoccl_dtype_t dt, Phase ph, const MultiArgs &a, int wg, int threads,
                            hipStream_t s, bool bf16_partials = false);
 // Copies: copy_tiles_of lays the row of tiles (call it before the launch) for a
@@ -286,8 +286,13 @@ hipError_t launch_multihop(hoccl_dtype_t dt, Phase ph, const MultiArgs &a, int w
 // launch can use.
 uint32_t copy_tiles_of(CopyArgs &a, int threads, int budget);
 uint32_t copy_tiles_of(FanArgs &a, int threads, int budget);
-hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s);
-hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s);
+hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s, size_t lds);
+hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s, size_t lds);
+// LDS that a launch asks for to bound the workgroups a CU holds, on the whole
+// chip and without a workgroup budget (else the caller asks for none).
+size_t fold_lds(hoccl_dtype_t dt, const FoldArgs &a, int threads);
+inline size_t copy_lds(const CopyArgs &, int, int) { return 0; }
+size_t copy_lds(const FanArgs &a, int wg, int threads);
 
 // Elements of the collective's dtype one thread covers in one pass of each
 // kernel's main loop.

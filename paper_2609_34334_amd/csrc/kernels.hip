@@ -883,43 +883,54 @@ size_t fold_elems_per_thread(hoccl_dtype_t dt) { return 16 / dtype_size(dt); }
 // against 27.3 by the kernel for any R; R = 5, n = 5,242,880 bf16: 54 against
 // 61).  More ranks would need more than the 100 or so scalar registers a
 // wave has.
-//
-// An all-reduce of three or more ranks writes as much as it reads, and HBM
-// takes that better when fewer workgroups are in flight and the windows they
-// write stay narrow: asking for LDS that the kernel does not use bounds them
-// to 1024 threads per CU (40 KiB of 160 for 256).  fp32, R = 3, n = 12,582,912:
-// 49.8 us so, 51.9 unbounded; bf16, R = 4, same n: 33.6 and 34.7; fp32, R = 4:
-// 65.4 and 67.2; bf16, R = 5, n = 5,000,011, bf16 partials: 17.5 and 18.3;
-// bf16, R = 8: 142 either way (its registers leave five workgroups).  With one
-// write for R reads, or two ranks, there would be too few bytes in flight:
-// reduce-scatter, R = 4, n = 6,000,000 bf16 43.1 so and 38.2 unbounded;
-// all-reduce, R = 2, n = 25,165,824 bf16 35.0 and 32.6.
 template <class T, int VE, int NR, bool RH>
-static hipError_t launch_fold_r(const FoldArgs &a, int wg, int threads, hipStream_t s) {
-    const size_t lds = a.write_all && NR >= 3 && threads <= 256 ? (size_t)threads * 160 : 0;
+static hipError_t launch_fold_r(const FoldArgs &a, int wg, int threads, hipStream_t s, size_t lds) {
     return launch((const void *)fold_kernel<T, VE, NR, NR, RH>, fit<NR>(a), wg, threads, s, lds);
 }
 
+// An all-reduce writes as much as it reads, and HBM takes that better when
+// fewer workgroups are in flight and the windows they write stay narrow:
+// asking for LDS that the kernel does not use bounds them to 1024 threads per
+// CU (40 KiB of 160 for 256).  It is asked for where it gained and nothing
+// else: all-reduces of three to five ranks of 16 MiB a rank or more (us,
+// bounded and not):
+//   R = 3, 48 MiB:  bf16 48.7 and 53.3, fp32 52.3 and 53.6
+//   R = 4, n = 16,777,216:  bf16 43.8 and 45.5, fp32 85.0 and 88.1
+//   R = 5, 48 MiB:  bf16 82.7 and 84.3, fp32 87.9 and 89.6
+//   R = 6, 48 MiB:  bf16 108 and 104;  R = 7, fp32 127 and 123;  R = 8 equal
+//   R = 3, 8 MiB:   bf16 10.2 and 9.9;  R = 4, 12 MB: 18.6 and 18.3
+//   reduce-scatter, R = 4, n = 6,000,000:  bf16 43.1 and 38.2
+// Beside a bf16 GEMM of 8192^3 it costs neither side anything (R = 4, 48 MiB:
+// 668 us a call and 665, the GEMM 9.1% slower and 8.6%; R = 3: 650 and 656).
+// On a stream with 32 of the CUs it does (R = 3, bf16: 228 us and 183; R = 4:
+// 278 and 264), so that the caller drops it there and under a workgroup
+// budget, where too few bytes are in flight already.  Above 256 threads the
+// same bound takes more than the 64 KiB a launch may ask for.
+size_t fold_lds(hoccl_dtype_t dt, const FoldArgs &a, int threads) {
+    const bool wide = a.R >= 3 && a.R <= 5 && a.total * dtype_size(dt) >= ((uint64_t)16 << 20);
+    return a.write_all && wide && threads <= 256 ? (size_t)threads * 160 : 0;
+}
+
 template <class T, int VE, bool RH = false>
-static hipError_t launch_fold_t(const FoldArgs &a, int wg, int threads, hipStream_t s) {
+static hipError_t launch_fold_t(const FoldArgs &a, int wg, int threads, hipStream_t s, size_t lds) {
     switch (a.R) {
-    case 2: return launch_fold_r<T, VE, 2, RH>(a, wg, threads, s);
-    case 3: return launch_fold_r<T, VE, 3, RH>(a, wg, threads, s);
-    case 4: return launch_fold_r<T, VE, 4, RH>(a, wg, threads, s);
-    case 5: return launch_fold_r<T, VE, 5, RH>(a, wg, threads, s);
-    case 6: return launch_fold_r<T, VE, 6, RH>(a, wg, threads, s);
-    case 7: return launch_fold_r<T, VE, 7, RH>(a, wg, threads, s);
-    case 8: return launch_fold_r<T, VE, 8, RH>(a, wg, threads, s);
-    default: return launch((const void *)fold_kernel<T, VE, 0, kMaxRanks, RH>, a, wg, threads, s);
+    case 2: return launch_fold_r<T, VE, 2, RH>(a, wg, threads, s, lds);
+    case 3: return launch_fold_r<T, VE, 3, RH>(a, wg, threads, s, lds);
+    case 4: return launch_fold_r<T, VE, 4, RH>(a, wg, threads, s, lds);
+    case 5: return launch_fold_r<T, VE, 5, RH>(a, wg, threads, s, lds);
+    case 6: return launch_fold_r<T, VE, 6, RH>(a, wg, threads, s, lds);
+    case 7: return launch_fold_r<T, VE, 7, RH>(a, wg, threads, s, lds);
+    case 8: return launch_fold_r<T, VE, 8, RH>(a, wg, threads, s, lds);
+    default: return launch((const void *)fold_kernel<T, VE, 0, kMaxRanks, RH>, a, wg, threads, s, lds);
     }
 }
 
 hipError_t launch_fold(hoccl_dtype_t dt, const FoldArgs &a, int wg, int threads, hipStream_t s,
-                       bool bf16_partials) {
-    if (dt == HOCCL_BF16 && bf16_partials) return launch_fold_t<TBF16, 8, true>(a, wg, threads, s);
-    if (dt == HOCCL_BF16) return launch_fold_t<TBF16, 8>(a, wg, threads, s);
-    if (dt == HOCCL_FP32) return launch_fold_t<TF32, 4>(a, wg, threads, s);
-    if (dt == HOCCL_INT32) return launch_fold_t<TI32, 4>(a, wg, threads, s);
+                       bool bf16_partials, size_t lds) {
+    if (dt == HOCCL_BF16 && bf16_partials) return launch_fold_t<TBF16, 8, true>(a, wg, threads, s, lds);
+    if (dt == HOCCL_BF16) return launch_fold_t<TBF16, 8>(a, wg, threads, s, lds);
+    if (dt == HOCCL_FP32) return launch_fold_t<TF32, 4>(a, wg, threads, s, lds);
+    if (dt == HOCCL_INT32) return launch_fold_t<TI32, 4>(a, wg, threads, s, lds);
     return hipErrorInvalidValue;
 }
 
@@ -963,7 +974,7 @@ static hipError_t launch_copy_as(const CopyArgs &a, int wg, int threads, hipStre
     if (a.nseg <= 32) return launch((const void *)copy_kernel<32, 1, U, NT>, fit_copy<32>(a), wg, threads, s);
     return launch((const void *)copy_kernel<kMaxCopySegs, 1, U, NT>, a, wg, threads, s);
 }
-hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s) {
+hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s, size_t) {
     if (a.unroll != 1) return launch_copy_as<kDeepCopy, false>(a, wg, threads, s);
     // Reading more than the 256 MB last-level cache holds, little of it can be
     // there from an earlier write, and non-temporal loads are the faster ones:
@@ -992,12 +1003,22 @@ static hipError_t launch_fan_u(const FanArgs &a, int wg, int threads, size_t lds
 // With two or three destinations there are too few bytes in flight then: two
 // 16 MiB shards take 21.7 us so and 16.2 with four vectors and no bound;
 // three 8 MiB shards 19.6 and 16.3; four 16 MiB shards 49.0 and 49.3.
-hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s) {
-    if (a.unroll != 1) return launch_fan_u<kDeepCopy>(a, wg, threads, 0, s);
-    // The kernel uses no LDS; asking for it bounds how many workgroups a CU
-    // holds (64 KiB of 160 KiB: two of 256 threads).
-    const size_t lds = threads <= 256 ? (size_t)threads << 8 : 0;
+hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s, size_t lds) {
+    if (a.unroll != 1) return launch_fan_u<kDeepCopy>(a, wg, threads, lds, s);
     return launch_fan_u<1>(a, wg, threads, lds, s);
+}
+
+// The kernel uses no LDS; asking for it bounds how many workgroups a CU holds
+// (64 KiB of 160 KiB: two of 256 threads).  Where a launch has no more than
+// that for each of 256 CUs it asks for none.  Eight 16 MiB shards take 188 us
+// so and 214 without, eight of 48 MiB 565 and 698.  Beside a bf16 GEMM of
+// 8192^3 the 16 MiB gather takes 460 us and 821, the GEMM being 66% and 26%
+// slower meanwhile, which is 0.18 and 0.17 ms of its time per gather.  On a
+// stream with 32 of the CUs the bound costs (638 us and 366): the caller drops
+// it there and under a workgroup budget.  Above 256 threads it would take more
+// than the 64 KiB a launch may ask for.
+size_t copy_lds(const FanArgs &a, int wg, int threads) {
+    return a.unroll == 1 && wg > 512 && threads <= 256 ? (size_t)threads << 8 : 0;
 }
 
 }  // namespace hoccl

@@ -17,3 +17,9 @@ extern "C" int occupy_launch(int blocks, uint64_t ticks, hipStream_t stream) {
     hipLaunchKernelGGL(occupy_kernel, dim3((unsigned)blocks), dim3(1024), 0, stream, ticks);
     return (int)hipGetLastError();
 }
+
+// The same by blocks of one wave that each hold `lds` bytes of LDS.
+extern "C" int occupy_lds_launch(int blocks, uint64_t ticks, unsigned lds, hipStream_t stream) {
+    hipLaunchKernelGGL(occupy_kernel, dim3((unsigned)blocks), dim3(64), lds, stream, ticks);
+    return (int)hipGetLastError();
+}
