@@ -162,7 +162,8 @@ typedef struct {
     int threads_per_workgroup;  /* 64..1024, multiple of 64; 0 = 256           */
     size_t chunk_bytes;         /* split copies into pieces of this size
                                    (>= 4096); 0 = no split, or the automatic
-                                   split of the SDMA copy path                 */
+                                   split of the SDMA copy path; the CU copy
+                                   kernel has tiles of its own and joins them  */
     int copy_streams;           /* copy streams of the HIP path, 1..16; 0 = 8  */
     hoccl_copy_path_t copy_path;
     int allgather_direct;       /* 1 (default): every rank copies each shard

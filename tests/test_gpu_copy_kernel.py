@@ -1,8 +1,13 @@
-"""The CU copy kernel's launches: what the statistics report of them."""
+"""The CU copy kernel's launches: what the statistics report of them, which
+copies share one, and results bit for bit."""
+import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2609_34334_amd as hc
+import workloads as W
+from gpu_util import assert_bitwise, check_canaries, from_dev, padded, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -34,3 +39,46 @@ def test_statistics_hold_the_workgroups_launched(nbytes, budget):
         assert s["cus_used_max"] == min(s["workgroups_per_step"], ncu)
     if nbytes > 64 << 20:
         assert s["cus_used_max"] == ncu
+
+
+def gather(R, n, lead=3):
+    """An all-gather of byte shards into windows at odd offsets, checked with
+    canaries; returns the call's statistics."""
+    x = [W.random_bits(1100 + R, r, n, 1) for r in range(R)]
+    pads = [padded(R * n, hc.UINT8, lead=lead + r) for r in range(R)]
+    hc.allgather([to_dev(a, hc.UINT8) for a in x], [w for _, w in pads])
+    torch.cuda.synchronize()
+    whole = np.concatenate(x)
+    for r, (full, win) in enumerate(pads):
+        check_canaries(full, lead + r, R * n, hc.UINT8)
+        assert_bitwise(from_dev(win, hc.UINT8), whole, f"AG R={R} n={n} r={r}")
+    return hc.last_stats()
+
+
+@pytest.mark.parametrize("R", [2, 5, 8])
+@pytest.mark.parametrize("chunk", [4096, 5000, 65_537])
+def test_pieces_of_a_copy_share_its_launch(R, chunk):
+    """chunk_bytes cuts copies for the engines; the kernel joins the pieces, so
+    that a gather is one launch and reads a shard once."""
+    hc.set_config(copy_path="kernel", chunk_bytes=chunk)
+    assert gather(R, 131_075)["copy_kernel_launches"] == 1
+
+
+@pytest.mark.parametrize("cfg", [dict(a2a_schedule=1), dict(a2a_schedule=0)], ids=["staged", "direct"])
+def test_pieces_in_the_schedulers_order(cfg):
+    """The scheduler deals the pieces of several flows in turn: those of one
+    flow mostly don't follow each other."""
+    hc.set_config(copy_path="kernel", chunk_bytes=4096, **cfg)
+    R, n = 4, 20_001
+    x = [W.random_bits(1120, r, R * n, 1) for r in range(R)]
+    ref = [np.zeros(R * n, np.uint8) for _ in range(R)]
+    oracle.alltoall(x, ref, n, hc.UINT8)
+    out = hc.alltoall([to_dev(a, hc.UINT8) for a in x])
+    torch.cuda.synchronize()
+    for r in range(R):
+        assert_bitwise(from_dev(out[r], hc.UINT8), ref[r], f"A2A r={r}")
+
+
+def test_pieces_of_a_forwarding_gather():
+    hc.set_config(copy_path="kernel", chunk_bytes=4096, allgather_direct=0)
+    gather(5, 30_001)
