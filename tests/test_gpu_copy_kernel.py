@@ -82,3 +82,11 @@ def test_pieces_in_the_schedulers_order(cfg):
 def test_pieces_of_a_forwarding_gather():
     hc.set_config(copy_path="kernel", chunk_bytes=4096, allgather_direct=0)
     gather(5, 30_001)
+
+
+@pytest.mark.parametrize("R, launches", [(8, 1), (9, 1), (10, 1), (16, 1), (17, 2), (25, 4)])
+def test_no_destination_is_left_for_a_launch_of_its_own(R, launches):
+    """Segments of up to eight destinations, 32 to a launch: nine and 17 ranks
+    split their destinations evenly."""
+    hc.set_config(copy_path="kernel")
+    assert gather(R, 1003)["copy_kernel_launches"] == launches
