@@ -692,11 +692,10 @@ hoccl_status_t run_copies_kernel(DeviceState &st, const hoccl_config_t &cfg, con
     FanArgs fan;
     auto flush = [&](auto &a, auto launch) -> hoccl_status_t {
         if (a.nseg == 0) return HOCCL_OK;
-        const unsigned tiles = copy_tiles_of(a, threads, cfg.workgroups_per_step);
-        const int w = cfg.workgroups_per_step > 0 ? cfg.workgroups_per_step : (int)std::min(tiles, kMaxCopyWorkgroups);
+        const int w = (int)std::min(copy_layout(a, threads, cfg.workgroups_per_step), kMaxCopyWorkgroups);
         TimingPair *tp;
         TRY(timed_begin(st, cfg, s, &tp));
-        HIP_TRY(launch(a, w, threads, s, lds_for(st, cfg, s, copy_lds(a, w, threads))));
+        HIP_TRY(launch(a, w, threads, s, lds_for(st, cfg, s, copy_lds(a, threads))));
         TRY(timed_end(tp, s));
         t_stats.copy_kernel_launches++;
         wg = std::max(wg, w);

@@ -218,7 +218,7 @@ struct MultiArgsT {
 using MultiArgs = MultiArgsT<kMaxMultiSegs>;
 
 // A copy segment: one source and its nd destinations (at most ND).  `first`
-// is the segments' row of tiles (copy_tiles_of).
+// is the segments' row of tiles (copy_layout).
 template <int ND>
 struct CSegArgT {
     const void *src;
@@ -238,6 +238,7 @@ struct CopyArgsT {
     CSegArgT<ND> seg[CAP];
     uint32_t first[CAP + 1];
     uint32_t unroll;   // 16-byte vectors per thread of a tile
+    uint32_t row;      // the workgroups walk the row of tiles, not a segment each
     int nseg;
     uint32_t threads;  // per workgroup; set at the launch
 };
@@ -281,18 +282,17 @@ hipError_t launch_fold(hoccl_dtype_t dt, const FoldArgs &a, int wg, int threads,
                        hipStream_t s, bool bf16_partials = false, size_t lds = 0);
 hipError_t launch_multihop(hoccl_dtype_t dt, Phase ph, const MultiArgs &a, int wg, int threads,
                            hipStream_t s, bool bf16_partials = false);
-// Copies: copy_tiles_of lays the row of tiles (call it before the launch) for a
-// workgroup budget (0: none) and returns its length, the most workgroups the
-// launch can use.
-uint32_t copy_tiles_of(CopyArgs &a, int threads, int budget);
-uint32_t copy_tiles_of(FanArgs &a, int threads, int budget);
+// Copies: copy_layout lays a launch's tiles out (call it before the launch) for
+// a workgroup budget (0: none) and returns the workgroups to launch.
+uint32_t copy_layout(CopyArgs &a, int threads, int budget);
+uint32_t copy_layout(FanArgs &a, int threads, int budget);
 hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s, size_t lds);
 hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s, size_t lds);
 // LDS that a launch asks for to bound the workgroups a CU holds, on the whole
 // chip and without a workgroup budget (else the caller asks for none).
 size_t fold_lds(hoccl_dtype_t dt, const FoldArgs &a, int threads);
-inline size_t copy_lds(const CopyArgs &, int, int) { return 0; }
-size_t copy_lds(const FanArgs &a, int wg, int threads);
+inline size_t copy_lds(const CopyArgs &, int) { return 0; }
+size_t copy_lds(const FanArgs &a, int threads);
 
 // Elements of the collective's dtype one thread covers in one pass of each
 // kernel's main loop.

@@ -102,8 +102,8 @@ constexpr int kNtOnly = (HOCCL_NT_X ? 3 : 0) | (HOCCL_NT_FINAL ? 4 : 0);
 constexpr int kVeBf16Partial = 4;
 constexpr int kVeBf16Only = 8;
 constexpr int kVe32 = 4;
-constexpr int kDeepCopy = 4;  // vectors per thread of a deep copy tile (copy_tiles_of)
-constexpr int kWideFan = 4;   // destinations from which a copy is write-bound (launch_fan)
+constexpr int kDeepCopy = 4;  // vectors per thread of a deep copy tile (copy_layout)
+constexpr int kWideFan = 5;   // destinations from which a copy is write-bound (copy_layout)
 
 // Byte-aligned vectors.  The compute units take a 16-byte global access at any
 // byte address (the HSA target runs with unaligned access enabled), so the
@@ -647,11 +647,20 @@ __device__ __forceinline__ void copy_tiles(const CSegArgT<ND> &s, uint32_t at, b
     }
 }
 
-// The tiles of all segments form one row (segment s has tiles first[s] up to
-// first[s + 1]); block b takes tiles b, b + G, b + 2G, ... of it.
-template <int CAP, int ND, int U, bool NT_IN>
+// ROW: the tiles of all segments form one row (segment s has tiles first[s] up
+// to first[s + 1]); block b takes tiles b, b + G, b + 2G, ... of it.  Otherwise
+// every segment has blocks of its own that walk its tiles: one read of the
+// arguments serves a block, where a step along the row takes a search and a
+// read per segment.  copy_layout says which launch takes which.
+template <int CAP, int ND, int U, bool NT_IN, bool ROW>
 __global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP, ND>) {
     const CopyArgsT<CAP, ND> &a = kernargs<CopyArgsT<CAP, ND>>();
+    if constexpr (!ROW) {
+        for_each_segment<true>(a.nseg, false, [&](int seg, int lb, int nb) __attribute__((always_inline)) {
+            copy_tiles<U, ND, NT_IN>(a.seg[seg], (uint32_t)lb, lb == nb - 1, (uint32_t)nb, a.threads);
+        });
+        return;
+    }
     const uint32_t G = gridDim.x;
     for (uint32_t at = blockIdx.x; at < a.first[a.nseg];) {
         int lo = 0, hi = a.nseg;
@@ -934,48 +943,97 @@ hipError_t launch_fold(hoccl_dtype_t dt, const FoldArgs &a, int wg, int threads,
     return hipErrorInvalidValue;
 }
 
-// The row of tiles of a launch, each `unroll` vectors per thread; returns its
-// length.
+// Lays a launch out in tiles of `unroll` vectors per thread, in a row or
+// segment by segment, and returns the workgroups that take one tile each: all
+// tiles of the row, or as many for every segment as the longest one has.
 template <int CAP, int ND>
-static uint32_t lay_tiles(CopyArgsT<CAP, ND> &a, int threads, int unroll) {
+static uint32_t lay_tiles(CopyArgsT<CAP, ND> &a, int threads, int unroll, bool row) {
     const uint64_t tile = (uint64_t)threads * 16 * (uint64_t)unroll;
-    uint32_t at = 0;
+    uint32_t at = 0, longest = 0;
     for (int k = 0; k < a.nseg; ++k) {
+        const uint32_t tiles = (uint32_t)((a.seg[k].bytes + tile - 1) / tile);
         a.first[k] = at;
-        at += (uint32_t)((a.seg[k].bytes + tile - 1) / tile);
+        at += tiles;
+        longest = tiles > longest ? tiles : longest;
     }
     a.first[a.nseg] = at;
     a.unroll = (uint32_t)unroll;
-    return at;
+    a.row = row;
+    return row ? at : longest * (uint32_t)a.nseg;
 }
 
-// Segments of one destination: tiles of one vector per thread, a workgroup
-// each.  Deeper tiles read and write a wider window at once: with 1, 2 and 4
-// vectors the EP all-to-all(v) takes 194, 195 and 213 us, one of 2.4 GB 752,
-// 791 and 855, a 1 GiB send/recv 346, 349 and 361 (eight 16 MiB messages 46
-// each).  Under a workgroup budget that leaves each several tiles, the bytes
-// in flight per wave set the rate instead (8 workgroups: 2.5 ms for 512 MiB
-// with 4 vectors, 4.2 with 2), so the tiles are deep.
-uint32_t copy_tiles_of(CopyArgs &a, int threads, int budget) {
-    const uint32_t tiles = lay_tiles(a, threads, 1);
-    return budget > 0 && (uint32_t)budget < tiles ? lay_tiles(a, threads, kDeepCopy) : tiles;
+template <int CAP, int ND>
+static uint64_t bytes_written(const CopyArgsT<CAP, ND> &a) {
+    uint64_t n = 0;
+    for (int k = 0; k < a.nseg; ++k) n += a.seg[k].bytes * (uint64_t)a.seg[k].nd;
+    return n;
 }
-// Segments of several destinations: see launch_fan.
-uint32_t copy_tiles_of(FanArgs &a, int threads, int) {
+
+// Segments of one destination.  Times in us over buffers the caches hold and
+// over rotating ones, as "row, one vector / row, four / segment by segment".
+// * Equal segments, up to 16 MiB in all, or of up to 1 MiB each and 64 MiB in
+//   all: segment by segment, four vectors (all-to-all at R = 8, 256 KiB a
+//   pair 6.6, 9.0 / 5.5, 8.7 / 4.7, 7.6; 1 MiB 22.3, 26.5 / 18.9, 26.6 / 17.4,
+//   26.3; a 2 MiB pair at R = 2 3.7, 4.7 / 3.3, 4.3 / 3.2, 4.1).  Longer ones
+//   are too few windows for HBM (eight of 4 MiB 10.7, 13.9 / 9.0, 13.8 / 9.0,
+//   15.5), unequal ones leave workgroups idle.
+// * From 16 to 48 MiB: the row, four vectors (an all-to-all(v) of 35 MB
+//   12.0, 12.2 / 10.6, 11.4 / -).  Beyond, one vector, as deeper tiles read
+//   and write a wider window at once (64 MiB in four segments 18.0, 23.4 /
+//   17.6, 24.7 / 17.3, 26.4; the EP all-to-all(v) 194 with one, 213 with
+//   four), and below 16 MiB where segments are unequal (64 of 40,000 bytes on
+//   average, skewed: 3.0, 3.5 / 3.3, 4.3 / 3.3, 4.3).
+// * A workgroup budget of fewer than those: deep tiles, as the bytes in flight
+//   per wave then set the rate (8 workgroups: 2.5 ms for 512 MiB with 4
+//   vectors, 4.2 with 2), segment by segment for equal segments (all-to-all at
+//   R = 8 on 64 workgroups, 512 KiB a pair: - / 33.5, 43.1 / 14.9, 29.0; on 8,
+//   64 KiB: - / 25.7, 36.2 / 10.9, 16.1), else the row (skewed, 1 MB a pair on
+//   64: - / 28.9, 29.8 / 96, 96).
+uint32_t copy_layout(CopyArgs &a, int threads, int budget) {
+    constexpr uint64_t MiB = 1u << 20;
+    const uint64_t bytes = bytes_written(a);
+    uint64_t longest = 0;
+    for (int k = 0; k < a.nseg; ++k) longest = a.seg[k].bytes > longest ? a.seg[k].bytes : longest;
+    const bool even = longest * (uint64_t)a.nseg * 4 <= bytes * 5;
+    uint32_t wg;
+    if (even && (bytes <= 16 * MiB || (longest <= MiB && bytes <= 64 * MiB)))
+        wg = lay_tiles(a, threads, kDeepCopy, false);
+    else
+        wg = lay_tiles(a, threads, bytes > 16 * MiB && bytes <= 48 * MiB ? kDeepCopy : 1, true);
+    if (budget > 0 && (uint32_t)budget < wg) lay_tiles(a, threads, kDeepCopy, !even);
+    return budget > 0 ? (uint32_t)budget : wg;
+}
+
+// Segments of several destinations, whose tiles each write several times
+// themselves; times as above, row / segment by segment.
+// * Up to 16 MiB written: segment by segment, one vector (gathers of 64 KiB
+//   shards at R = 8 3.3, 2.9 / 3.0, 2.8 and R = 3 3.2, 3.5 / 2.4, 2.6).
+// * Beyond, the row: one vector under the bound of copy_lds from kWideFan
+//   destinations on, where writes dominate (eight 16 MiB shards 180 us; 207
+//   without the bound; 239 with four vectors), four vectors and no bound for
+//   fewer, which leave too few bytes in flight so (two 16 MiB shards 13.7 and
+//   21.0 with one vector, four 1 MiB shards 4.7 and 5.2).
+// * A budget of fewer workgroups: the row with four vectors (eight 16 MiB
+//   shards on 8 workgroups 1290, with one vector 1700; on 64 196 and 231).
+uint32_t copy_layout(FanArgs &a, int threads, int budget) {
     int nd = 0;
     for (int k = 0; k < a.nseg; ++k) nd = a.seg[k].nd > nd ? a.seg[k].nd : nd;
-    return lay_tiles(a, threads, nd >= kWideFan ? 1 : kDeepCopy);
+    const bool row = bytes_written(a) > ((uint64_t)16 << 20);
+    const uint32_t wg = lay_tiles(a, threads, row && nd < kWideFan ? kDeepCopy : 1, row);
+    if (budget > 0 && (uint32_t)budget < wg) lay_tiles(a, threads, kDeepCopy, true);
+    return budget > 0 ? (uint32_t)budget : wg;
 }
 
 // Copy launches of up to 8, 32 or 128 segments (250 bytes to 4 KiB of arguments).
-template <int U, bool NT>
+template <int U, bool NT, bool ROW>
 static hipError_t launch_copy_as(const CopyArgs &a, int wg, int threads, hipStream_t s) {
-    if (a.nseg <= 8) return launch((const void *)copy_kernel<8, 1, U, NT>, fit_copy<8>(a), wg, threads, s);
-    if (a.nseg <= 32) return launch((const void *)copy_kernel<32, 1, U, NT>, fit_copy<32>(a), wg, threads, s);
-    return launch((const void *)copy_kernel<kMaxCopySegs, 1, U, NT>, a, wg, threads, s);
+    if (a.nseg <= 8) return launch((const void *)copy_kernel<8, 1, U, NT, ROW>, fit_copy<8>(a), wg, threads, s);
+    if (a.nseg <= 32) return launch((const void *)copy_kernel<32, 1, U, NT, ROW>, fit_copy<32>(a), wg, threads, s);
+    return launch((const void *)copy_kernel<kMaxCopySegs, 1, U, NT, ROW>, a, wg, threads, s);
 }
 hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s, size_t) {
-    if (a.unroll != 1) return launch_copy_as<kDeepCopy, false>(a, wg, threads, s);
+    if (!a.row) return launch_copy_as<kDeepCopy, false, false>(a, wg, threads, s);
+    if (a.unroll != 1) return launch_copy_as<kDeepCopy, false, true>(a, wg, threads, s);
     // Reading more than the 256 MB last-level cache holds, little of it can be
     // there from an earlier write, and non-temporal loads are the faster ones:
     // 204 us for the EP all-to-all(v) (608 MB) instead of 217, 747 for a 2 GiB
@@ -983,42 +1041,32 @@ hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s, si
     // cache they are slower: a pipeline schedule of 16 MiB messages, each read
     // soon after it was written, would take 1234 us instead of 1119, a 64 MiB
     // copy 32.8 instead of 28.3.
-    const uint64_t bytes = (uint64_t)a.first[a.nseg] * (uint64_t)threads * 16;
-    return bytes > ((uint64_t)256 << 20) ? launch_copy_as<1, true>(a, wg, threads, s)
-                                         : launch_copy_as<1, false>(a, wg, threads, s);
+    return bytes_written(a) > ((uint64_t)256 << 20) ? launch_copy_as<1, true, true>(a, wg, threads, s)
+                                                    : launch_copy_as<1, false, true>(a, wg, threads, s);
 }
 
-template <int U>
-static hipError_t launch_fan_u(const FanArgs &a, int wg, int threads, size_t lds, hipStream_t s) {
+template <int U, bool ROW>
+static hipError_t launch_fan_as(const FanArgs &a, int wg, int threads, hipStream_t s, size_t lds) {
     if (a.nseg <= 8)
-        return launch((const void *)copy_kernel<8, kMaxFan, U, false>, fit_copy<8>(a), wg, threads, s, lds);
-    return launch((const void *)copy_kernel<kMaxFanSegs, kMaxFan, U, false>, a, wg, threads, s, lds);
+        return launch((const void *)copy_kernel<8, kMaxFan, U, false, ROW>, fit_copy<8>(a), wg, threads, s, lds);
+    return launch((const void *)copy_kernel<kMaxFanSegs, kMaxFan, U, false, ROW>, a, wg, threads, s, lds);
 }
-// Segments of several destinations.  From kWideFan destinations up the writes
-// dominate, and HBM takes them best when few workgroups are in flight, each
-// one vector deep per stream, so that the window they write to stays narrow:
-// the gather of eight 16 MiB shards takes 193 us (6.3 TB/s) with two
-// workgroups of 256 per CU and one vector, 239 with four vectors and as many
-// workgroups as fit, and took 347 as 64 copies that each read their source.
-// With two or three destinations there are too few bytes in flight then: two
-// 16 MiB shards take 21.7 us so and 16.2 with four vectors and no bound;
-// three 8 MiB shards 19.6 and 16.3; four 16 MiB shards 49.0 and 49.3.
 hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s, size_t lds) {
-    if (a.unroll != 1) return launch_fan_u<kDeepCopy>(a, wg, threads, lds, s);
-    return launch_fan_u<1>(a, wg, threads, lds, s);
+    if (!a.row) return launch_fan_as<1, false>(a, wg, threads, s, lds);
+    if (a.unroll != 1) return launch_fan_as<kDeepCopy, true>(a, wg, threads, s, lds);
+    return launch_fan_as<1, true>(a, wg, threads, s, lds);
 }
 
 // The kernel uses no LDS; asking for it bounds how many workgroups a CU holds
-// (64 KiB of 160 KiB: two of 256 threads).  Where a launch has no more than
-// that for each of 256 CUs it asks for none.  Eight 16 MiB shards take 188 us
+// (64 KiB of 160 KiB: two of 256 threads).  Eight 16 MiB shards take 188 us
 // so and 214 without, eight of 48 MiB 565 and 698.  Beside a bf16 GEMM of
 // 8192^3 the 16 MiB gather takes 460 us and 821, the GEMM being 66% and 26%
 // slower meanwhile, which is 0.18 and 0.17 ms of its time per gather.  On a
 // stream with 32 of the CUs the bound costs (638 us and 366): the caller drops
 // it there and under a workgroup budget.  Above 256 threads it would take more
 // than the 64 KiB a launch may ask for.
-size_t copy_lds(const FanArgs &a, int wg, int threads) {
-    return a.unroll == 1 && wg > 512 && threads <= 256 ? (size_t)threads << 8 : 0;
+size_t copy_lds(const FanArgs &a, int threads) {
+    return a.row && a.unroll == 1 && threads <= 256 ? (size_t)threads << 8 : 0;
 }
 
 }  // namespace hoccl

@@ -90,3 +90,66 @@ def test_no_destination_is_left_for_a_launch_of_its_own(R, launches):
     split their destinations evenly."""
     hc.set_config(copy_path="kernel")
     assert gather(R, 1003)["copy_kernel_launches"] == launches
+
+
+def random_bytes(n, seed, lead=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randint(0, 256, (lead + n,), generator=g, device="cuda", dtype=torch.uint8)[lead:]
+
+
+def same(full, lead, n, parts, what):
+    """The window holds `parts` one after another and the canaries around it
+    stand (compared on the device: these buffers are large)."""
+    assert bool((full[:lead] == 0x5A).all()) and bool((full[lead + n:] == 0x5A).all()), f"{what}: canary overwritten"
+    at = lead
+    for p in parts:
+        assert torch.equal(full[at:at + p.numel()], p), what
+        at += p.numel()
+    assert at == lead + n
+
+
+# Which form a copy launch takes goes by its bytes, the evenness of its segments
+# and the workgroup budget: each form at odd lengths and offsets, below and
+# above every limit.
+@pytest.mark.parametrize("wg", [0, 5, 300])
+@pytest.mark.parametrize("R, n", [(2, 4_000_037), (2, (9 << 20) + 3), (2, (25 << 20) + 1), (3, (5 << 20) + 7)])
+def test_messages_in_every_form(R, n, wg):
+    hc.set_config(copy_path="kernel", workgroups_per_step=wg)
+    send = [random_bytes(n, 1200 + r, lead=5 * r + 1) for r in range(R)]
+    pads = [padded(n, hc.UINT8, lead=3 + r) for r in range(R)]
+    hc.sendrecv(send, [w for _, w in pads], [(r + 1) % R for r in range(R)])
+    torch.cuda.synchronize()
+    for r, (full, _) in enumerate(pads):
+        same(full, 3 + r, n, [send[(r - 1) % R]], f"SR R={R} n={n} r={r}")
+
+
+@pytest.mark.parametrize("wg", [0, 5, 64, 300])
+@pytest.mark.parametrize("R, n, skew", [(8, 70_001, 0), (8, (1 << 20) - 5, 0), (8, (1 << 20) + 3, 0),
+                                        (8, 200_000, 1), (6, 900_000, 1), (12, 3000, 1)])
+def test_all_to_all_in_every_form(R, n, skew, wg):
+    hc.set_config(copy_path="kernel", workgroups_per_step=wg)
+    rng = np.random.default_rng(1210 + R)
+    counts = [int(n * (4 * rng.random() ** 6 if skew else 1)) for _ in range(R * R)]
+    sd = [sum(counts[s * R:s * R + d]) for s in range(R) for d in range(R)]
+    rd = [sum(counts[q * R + d] for q in range(s)) for s in range(R) for d in range(R)]
+    send = [random_bytes(sum(counts[s * R:(s + 1) * R]), 1220 + s, lead=s) for s in range(R)]
+    sizes = [sum(counts[s * R + d] for s in range(R)) for d in range(R)]
+    pads = [padded(m, hc.UINT8, lead=1 + d) for d, m in enumerate(sizes)]
+    hc.alltoallv(send, counts, sd, [w for _, w in pads], rd)
+    torch.cuda.synchronize()
+    for d, (full, _) in enumerate(pads):
+        parts = [send[s][sd[s * R + d]:sd[s * R + d] + counts[s * R + d]] for s in range(R)]
+        same(full, 1 + d, sizes[d], parts, f"A2AV R={R} n={n} d={d}")
+
+
+@pytest.mark.parametrize("wg", [0, 5, 300])
+@pytest.mark.parametrize("R, n", [(3, 100_003), (3, (3 << 20) + 1), (4, (2 << 20) - 1), (5, (1 << 20) + 9),
+                                  (8, 262_143), (8, 262_147), (9, 1_000_003)])
+def test_gathers_in_every_form(R, n, wg):
+    hc.set_config(copy_path="kernel", workgroups_per_step=wg)
+    send = [random_bytes(n, 1230 + r, lead=7 * r + 1) for r in range(R)]
+    pads = [padded(R * n, hc.UINT8, lead=2 + r) for r in range(R)]
+    hc.allgather(send, [w for _, w in pads])
+    torch.cuda.synchronize()
+    for r, (full, _) in enumerate(pads):
+        same(full, 2 + r, R * n, send, f"AG R={R} n={n} r={r}")
