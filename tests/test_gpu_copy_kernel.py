@@ -153,3 +153,33 @@ def test_gathers_in_every_form(R, n, wg):
     torch.cuda.synchronize()
     for r, (full, _) in enumerate(pads):
         same(full, 2 + r, R * n, send, f"AG R={R} n={n} r={r}")
+
+
+@pytest.mark.parametrize("wg", [0, 300])
+def test_launches_beyond_the_last_level_cache(wg):
+    """More than 256 MiB in one launch: read past the caches without a budget,
+    by equal and by unequal segments at odd lengths and offsets."""
+    hc.set_config(copy_path="kernel", workgroups_per_step=wg)
+    n = (129 << 20) + 5
+    send = [random_bytes(n, 1240 + r, lead=3 + 2 * r) for r in range(2)]
+    pads = [padded(n, hc.UINT8, lead=1 + r) for r in range(2)]
+    hc.sendrecv(send, [w for _, w in pads], [1, 0])
+    torch.cuda.synchronize()
+    assert hc.last_stats()["copy_kernel_launches"] == 1
+    for r, (full, _) in enumerate(pads):
+        same(full, 1 + r, n, [send[1 - r]], f"SR r={r}")
+    del send, pads
+    R = 8
+    rng = np.random.default_rng(1250)
+    counts = [int(v) for v in rng.integers(4_000_001, 5_000_000, R * R)]
+    sd = [sum(counts[s * R:s * R + d]) for s in range(R) for d in range(R)]
+    rd = [sum(counts[q * R + d] for q in range(s)) for s in range(R) for d in range(R)]
+    send = [random_bytes(sum(counts[s * R:(s + 1) * R]), 1260 + s, lead=s) for s in range(R)]
+    sizes = [sum(counts[s * R + d] for s in range(R)) for d in range(R)]
+    assert sum(sizes) > 256 << 20
+    pads = [padded(m, hc.UINT8, lead=1 + d) for d, m in enumerate(sizes)]
+    hc.alltoallv(send, counts, sd, [w for _, w in pads], rd)
+    torch.cuda.synchronize()
+    for d, (full, _) in enumerate(pads):
+        parts = [send[s][sd[s * R + d]:sd[s * R + d] + counts[s * R + d]] for s in range(R)]
+        same(full, 1 + d, sizes[d], parts, f"A2AV d={d}")
