@@ -332,7 +332,9 @@ typedef struct {
                                    with the host-function handshake            */
     hoccl_copy_path_t copy_path_used;
     unsigned long long hbm_bytes_algorithmic; /* bytes every step must read
-                                   and write in HBM, summed over the call      */
+                                   and write in HBM, summed over the call; the
+                                   CU copy kernel reads a source once for up to
+                                   eight destinations                          */
     double host_enqueue_us;     /* host time spent inside the call             */
     /* ---- extensions ---- */
     int copy_kernel_launches;   /* CU copy kernel launches enqueued            */

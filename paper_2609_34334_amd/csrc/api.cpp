@@ -681,9 +681,10 @@ void flows_of(const Plan &p, const Buffers &B, int level, std::vector<Flow> &out
 // no destination is left over for a launch of its own (the gather of nine 4 KiB
 // shards: 4.5 us with the ninth destination in a second launch, 2.8 in one; of
 // nine 256 KiB shards 7.4 and 5.2).  `wg` is raised to the most workgroups of
-// any launch here.
+// any launch here, `unread` by the bytes that sharing saves the plan's reads.
 hoccl_status_t run_copies_kernel(DeviceState &st, const hoccl_config_t &cfg, const Plan &p,
-                                 const Buffers &B, hipStream_t s, int &wg, int threads) {
+                                 const Buffers &B, hipStream_t s, int &wg, int threads,
+                                 unsigned long long &unread) {
     int maxlevel = 0;
     for (const CopyOp &c : p.copies) maxlevel = std::max(maxlevel, c.level);
     std::vector<Flow> flows;
@@ -724,8 +725,9 @@ hoccl_status_t run_copies_kernel(DeviceState &st, const hoccl_config_t &cfg, con
                 g.bytes = f.bytes;
                 g.nd = (int)((k - i + segs - 1) / segs);
                 for (int q = 0; q < kMaxFan; ++q) g.dst[q] = q < g.nd ? flows[i + (size_t)q].dst : nullptr;
-                if (fan.nseg == kMaxFanSegs) TRY(flush(fan, launch_fan));
+                unread += (unsigned long long)f.bytes * (unsigned long long)(g.nd - 1);
                 i += (size_t)g.nd;
+                if (fan.nseg == kMaxFanSegs) TRY(flush(fan, launch_fan));
             }
         }
         TRY(flush(one, launch_copy));
@@ -799,7 +801,8 @@ size_t auto_chunk_bytes(const DeviceState &st, const hoccl_config_t &cfg, hoccl_
 // Enqueues a plan's reductions and copies on `s` by the chosen copy path.
 hoccl_status_t enqueue_body(DeviceState &st, const hoccl_config_t &cfg, const Plan &p,
                             const Buffers &B, hipStream_t s, hoccl_copy_path_t path, int handshake,
-                            bool capturing, bool has_copies, int &wg, int threads) {
+                            bool capturing, bool has_copies, int &wg, int threads,
+                            unsigned long long &unread) {
     if (has_copies && path == HOCCL_COPY_SDMA && !capturing && p.ngroups > 1 &&
         !p.reduce_steps.empty()) {
         TRY(run_engine_groups(st, cfg, p, B, s, wg, threads, handshake));
@@ -848,7 +851,7 @@ hoccl_status_t enqueue_body(DeviceState &st, const hoccl_config_t &cfg, const Pl
         TRY(run_reductions(st, cfg, p, B, s, wg, threads, has_copies && path == HOCCL_COPY_HIP));
         if (has_copies) {
             if (path == HOCCL_COPY_KERNEL)
-                TRY(run_copies_kernel(st, cfg, p, B, s, wg, threads));
+                TRY(run_copies_kernel(st, cfg, p, B, s, wg, threads, unread));
             else
                 TRY(run_copies_hip(st, cfg, p, B, s));
         }
@@ -952,8 +955,9 @@ hoccl_status_t execute(Build build, bool in_place, const Buffers &B0, hipStream_
     }
     // From here on kernels may be on the stream: whatever happens, the next
     // workspace user on another stream must wait for them.
+    unsigned long long unread = 0;
     hoccl_status_t body = enqueue_body(st, cfg, p, B, s, path, handshake, capturing, has_copies, wg,
-                                       threads);
+                                       threads, unread);
     if (g_debug)
         std::fprintf(stderr, "hoccl: device %d stream %p workgroups %d copy_path %d%s plan %s\n",
                      st.device, (void *)s, wg, (int)path, capturing ? " (captured)" : "",
@@ -984,7 +988,7 @@ hoccl_status_t execute(Build build, bool in_place, const Buffers &B0, hipStream_
     t_stats.cus_used_max = cus;
     t_stats.copy_path_used = has_copies ? path : HOCCL_COPY_AUTO;
     t_stats.reduce_algo_used = p.has_fold ? HOCCL_REDUCE_DIRECT : HOCCL_REDUCE_RING;
-    t_stats.hbm_bytes_algorithmic = p.hbm_bytes;
+    t_stats.hbm_bytes_algorithmic = p.hbm_bytes - unread;
     t_stats.copy_bytes = p.copy_bytes;
     t_stats.host_enqueue_us =
         std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count();

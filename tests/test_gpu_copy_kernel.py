@@ -41,6 +41,25 @@ def test_statistics_hold_the_workgroups_launched(nbytes, budget):
         assert s["cus_used_max"] == ncu
 
 
+def test_statistics_count_a_shared_read_once():
+    """Nine ranks read every shard twice (for five destinations and four) and
+    write it nine times; a copy of its own per destination reads it nine times."""
+    R, n = 9, 4096
+    send = [torch.zeros(n, dtype=torch.uint8, device="cuda") for _ in range(R)]
+    recv = [torch.empty(R * n, dtype=torch.uint8, device="cuda") for _ in range(R)]
+    for path, reads in (("kernel", 2), ("hip", R)):
+        hc.set_config(copy_path=path)
+        hc.allgather(send, recv)
+        torch.cuda.synchronize()
+        s = hc.last_stats()
+        assert s["hbm_bytes_algorithmic"] == R * n * (reads + R), path
+        assert s["copy_bytes"] == R * R * n
+    hc.set_config(copy_path="kernel")
+    hc.sendrecv(send, recv=[torch.empty_like(t) for t in send], peers=[(r + 1) % R for r in range(R)])
+    torch.cuda.synchronize()
+    assert hc.last_stats()["hbm_bytes_algorithmic"] == 2 * R * n
+
+
 def gather(R, n, lead=3):
     """An all-gather of byte shards into windows at odd offsets, checked with
     canaries; returns the call's statistics."""
