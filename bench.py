@@ -6,10 +6,12 @@ virtual ranks, fp32 accumulation, 1/8 shard out per rank -- with inputs
 resident in HBM.  One step is one reduce-scatter; W untimed steps, then K
 timed steps bracketed by device synchronisation.
 
-Also printed in the same JSON line:
+Also in the JSON line:
   * roofline of the dominant kernel (the ring reduce-step kernel), from HIP
     events recorded around every launch on the stream it is launched on;
-  * cpu_baseline: the CPU oracle on the same workload, single thread;
+  * cpu_baseline: the CPU oracle on the same workload, single thread.
+Printed before it, as a JSON line on stderr (it is tens of KB, and a reader of
+the last line of stdout should not have to hold it):
   * extra: the other collectives of the hot path on their own workloads
     (all-reduce fp32, FSDP all-gather, PP send/recv, EP all-to-all(v) with a
     concurrent bf16 GEMM), each with algbw/busbw, %HBM peak and CUs used;
@@ -2037,8 +2039,8 @@ def main():
                      "measured_copy_ceiling": ceiling,
                      "frac_of_measured_copy_ceiling": round(rs["achieved"] / ceiling, 4)},
         "cpu_baseline": cpu,
-        "extra": extra,
     }
+    print(json.dumps({"extra": extra}), file=sys.stderr, flush=True)
     print(json.dumps(out), flush=True)
 
 
