@@ -506,8 +506,8 @@ hoccl_status_t hoccl_alltoallv(const void *const *send,
  *   HOCCL_HOP_ONLY    partial bf16, out bf16 (a two-rank fold, rounded once)
  * `local` is bf16 throughout.  For int32 and fp32 every operand has the
  * dtype and the four hops compute the same thing.  All three are device
- * pointers of count elements, any alignment (16-byte aligned runs at full
- * speed).  `out` may be `partial` or `local` itself when its element size
+ * pointers of count elements, any alignment (buffers that start on a 128-byte
+ * line are the fastest).  `out` may be `partial` or `local` itself when its element size
  * is the same (the in-place update of a partial); any other overlap is
  * HOCCL_ERR_INVALID_ARG.  Launch shape from workgroups_per_step and
  * threads_per_workgroup as for the collectives; no workspace, no copies,

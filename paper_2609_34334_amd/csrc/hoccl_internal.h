@@ -181,7 +181,7 @@ constexpr int kMaxRanks = 64;
 // that has not started yet, and the enqueueing thread waits once about 1 MB
 // of them is pending (measured on MI355X).  With 2 KiB of slots, some 450
 // launches queued behind unfinished work stall the caller; an 8-rank ring
-// step passes 264 bytes (plus the runtime's own 256 bytes of hidden
+// step passes 272 bytes (plus the runtime's own 256 bytes of hidden
 // arguments), and about 1000 fit.
 struct RSegArg {
     const void *in0;

@@ -12,8 +12,14 @@
 //
 // All three are HBM-bound streams (about one add per 8-12 bytes), so they
 // use 16-byte vector loads and stores, a grid-stride loop over each segment
-// with several independent vectors in flight per thread, and no LDS and no
-// MFMA: the limit is memory bandwidth, not arithmetic.
+// with several independent vectors in flight per thread, and neither share
+// data through LDS nor need MFMA: the limit is memory bandwidth, not
+// arithmetic.  (Some launches ask for LDS all the same, to bound the
+// workgroups in flight: fold_lds, copy_lds.)
+//
+// Where a comment compares two forms of the code, both sides are from one run
+// of the code as it then was.  Later steps moved both, so that only the
+// difference holds.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -80,9 +86,8 @@ struct Pack {
 #ifndef HOCCL_FOLD_NT_OUT
 #define HOCCL_FOLD_NT_OUT 1
 #endif
-// Whether the CU copy's stores are non-temporal.  Normal ones make the EP
-// all-to-all(v) 231 us instead of 217 and a 128 MiB send/recv 47.1 instead of
-// 45.9.
+// Whether the CU copy's stores are non-temporal.  Normal ones made the EP
+// all-to-all(v) 6% slower and a 128 MiB send/recv 3%.
 #ifndef HOCCL_COPY_NT_OUT
 #define HOCCL_COPY_NT_OUT 1
 #endif
@@ -110,9 +115,9 @@ constexpr int kWideFan = 5;   // destinations from which a copy is write-bound (
 // same instruction serves aligned and misaligned operands.  A misaligned
 // stream costs almost nothing where HBM is the limit, as a wave's 1 KiB span
 // only touches one line more: the bf16 fold into shards of odd length takes
-// 27.3 us at R = 6, n = 1,398,103 (26.8 for n + 1) and 78.1 us at R = 8,
-// n = 3,145,727 (77.3), where an element-by-element fallback took 62.5 and
-// 98.6; four fused ring hops of the latter take 104 us instead of 170.
+// 2% longer at R = 6, n = 1,398,103 than at n + 1 and 1% at R = 8,
+// n = 3,145,727, where an element-by-element fallback took 2.3 and 1.3 times
+// as long, and 1.6 times for four fused ring hops of the latter.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2), aligned(1)));
 
@@ -160,9 +165,9 @@ __device__ __forceinline__ void stp(P *p, const P &x) {
 // cache line (128 bytes).  A wave's span of a line-aligned stream is whole
 // lines; from any other 16-byte boundary, every span shares its first and
 // last line with its neighbours', and the writes of both are parts of lines:
-// the gather of six shards of 3,333,333 bytes takes 21.2 us line-aligned and
-// 27.9 aligned to 16 bytes, an fp32 all-reduce of 1,500,007 elements at
-// R = 16 39.5 and 43.0, one of 2,100,001 bf16 at R = 12 23.9 and 25.8.
+// aligned to 16 bytes only, the gather of six shards of 3,333,333 bytes took
+// 32% longer, an fp32 all-reduce of 1,500,007 elements at R = 16 9%, one of
+// 2,100,001 bf16 at R = 12 8%.
 constexpr uint32_t kLineBytes = 128;
 template <typename S>
 __device__ __forceinline__ uint64_t head_of(const S *p, uint64_t n) {
@@ -173,10 +178,10 @@ __device__ __forceinline__ uint64_t head_of(const S *p, uint64_t n) {
 // The elements before the vectors (h of them) and after (from `tail` to n),
 // one per lane: f(k).  They go to the last block of the segment, from its last
 // lane down: that block's vectors mostly end before its lanes do, so that its
-// idle waves take them (the all-reduce at R = 16 above: 34.5 us, against 39.5
-// with the first block's lanes).  Every wave runs the loop's test, on purpose:
-// the eight-rank fold, whose waves all start with it, takes 71 us at
-// n = 3,145,728 (bf16), and 77 with a uniform branch around the loop.
+// idle waves take them (the all-reduce at R = 16 above: 13% less than with the
+// first block's lanes).  Every wave runs the loop's test, on purpose: the
+// eight-rank fold, whose waves all start with it, took 8% longer at
+// n = 3,145,728 (bf16) with a uniform branch around the loop.
 template <typename F>
 __device__ __forceinline__ void for_each_edge(uint64_t h, uint64_t tail, uint64_t n, int lb, int nb, uint32_t bd,
                                               F &&f) {
@@ -192,7 +197,7 @@ constexpr int kXcds = 8;
 // block walks several segments.  Otherwise
 // * IN_TURN: block b serves segment b % nseg.  The ring's steps take this
 //   one: at 8 ranks chunk j then stays on XCD j from step to step (headline:
-//   266.6 us, against 269.5 with runs of blocks).
+//   1 to 2% less than with runs of blocks).
 // * else a run of consecutive blocks serves each segment, so that the launch
 //   sweeps the segments one after another and the blocks in flight read and
 //   write a few narrow windows of memory instead of nseg times as many.  The
@@ -449,7 +454,7 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
 
     // A chunk of odd length leaves the inputs' phase and the output shard's
     // apart: the reads are kept aligned (R streams) and the one write is
-    // misaligned (R = 6, n = 1,398,103 bf16: 19.8 us, 21.2 the other way).
+    // misaligned (R = 6, n = 1,398,103 bf16: 7% less than the other way).
     const uint64_t h = head_of(src(0), n);
     const uint64_t nv = (n - h) / VE;
     const uint64_t tail = h + nv * VE;
@@ -518,9 +523,12 @@ __device__ __forceinline__ void fold_chunk(const FA &a, int j, int lb, int nb) {
     // so that one scalar wait and one memory latency serve KB ranks, and the
     // output pointers likewise.  With a scalar wait before every rank's load
     // and store, and cached accesses, an fp32 all-reduce of 1,500,007
-    // elements at R = 16 took 63 us (3.0 TB/s) instead of 48.6 (4.0), one
-    // of 6,291,456 bf16 at R = 32 178 instead of 157, and a reduce-scatter
-    // of 26 MB a rank (bf16, R = 16) 90.6 instead of 77.4 (5.8 TB/s).
+    // elements at R = 16 took 30% longer, one of 6,291,456 bf16 at R = 32 13%,
+    // and a reduce-scatter of 26 MB a rank (bf16, R = 16) 17%.  Where one call
+    // after another folds the same inputs, cached loads would be the faster
+    // ones (R = 9, 72 MB in all: 23.4 us instead of 28.9); over inputs that
+    // change they are not (31.4 instead of 30.0; R = 9, 432 MB 173 instead of
+    // 160).
     constexpr int KB = 8;
     for (uint64_t i = t; i < nv; i += stride) {
         A acc[VE];
@@ -685,8 +693,8 @@ __global__ void __launch_bounds__(1024) copy_kernel(CopyArgsT<CAP, ND>) {
 // also return errors left behind by unrelated earlier calls).
 // Sets a.threads: a kernel that read its workgroup size from the hidden
 // arguments would start every wave with a vector load of it and the wait (the
-// headline ring, whose waves make one pass each, took 262.4 us so, and takes
-// 253.6 with the size among the arguments' scalar loads).
+// headline ring, whose waves make one pass each, took 3% longer so than with
+// the size among the arguments' scalar loads).
 template <typename Args>
 static hipError_t launch(const void *kernel, Args a, int wg, int threads, hipStream_t s, size_t lds = 0) {
     a.threads = (uint32_t)threads;
@@ -737,7 +745,7 @@ static FoldArgsT<CAP> fit(const FoldArgs &a) {
     return b;
 }
 
-// Ring steps of up to 8 ranks (264 bytes of arguments) or up to 64 (2 KiB).
+// Ring steps of up to 8 ranks (272 bytes of arguments) or up to 64 (2 KiB).
 constexpr int kSmallSegs = 8;
 
 template <class T0, class T1, class TO, int VE, int U, int NT>
@@ -888,9 +896,8 @@ size_t reduce_step_elems_per_thread(hoccl_dtype_t dt, Phase ph, bool bf16_partia
 size_t fold_elems_per_thread(hoccl_dtype_t dt) { return 16 / dtype_size(dt); }
 
 // R up to 8 has a kernel of its own, whose arguments hold R ranks and whose
-// pointers all stay in scalar registers (R = 6, n = 1,398,103 bf16: 23.7 us,
-// against 27.3 by the kernel for any R; R = 5, n = 5,242,880 bf16: 54 against
-// 61).  More ranks would need more than the 100 or so scalar registers a
+// pointers all stay in scalar registers (R = 6, n = 1,398,103 bf16: 13% less
+// than by the kernel for any R; R = 5, n = 5,242,880 bf16: 11%).  More ranks would need more than the 100 or so scalar registers a
 // wave has.
 template <class T, int VE, int NR, bool RH>
 static hipError_t launch_fold_r(const FoldArgs &a, int wg, int threads, hipStream_t s, size_t lds) {
@@ -974,21 +981,21 @@ static uint64_t bytes_written(const CopyArgsT<CAP, ND> &a) {
 // * Equal segments, up to 16 MiB in all, or of up to 1 MiB each and 64 MiB in
 //   all: segment by segment, four vectors (all-to-all at R = 8, 256 KiB a
 //   pair 6.6, 9.0 / 5.5, 8.7 / 4.7, 7.6; 1 MiB 22.3, 26.5 / 18.9, 26.6 / 17.4,
-//   26.3; a 2 MiB pair at R = 2 3.7, 4.7 / 3.3, 4.3 / 3.2, 4.1).  Longer ones
-//   are too few windows for HBM (eight of 4 MiB 10.7, 13.9 / 9.0, 13.8 / 9.0,
-//   15.5), unequal ones leave workgroups idle.
-// * From 16 to 48 MiB: the row, four vectors (an all-to-all(v) of 35 MB
+//   26.3; a 2 MiB pair at R = 2 3.7, 4.7 / 3.3, 4.3 / 3.2, 4.1).  Few long
+//   segments walked side by side spread HBM's windows (64 MiB in four 18.0,
+//   23.4 / 17.6, 24.7 / 17.3, 26.4), unequal ones leave workgroups idle.
+// * From 16 to 48 MiB: the row, four vectors (an all-to-all(v) of 36 MB
 //   12.0, 12.2 / 10.6, 11.4 / -).  Beyond, one vector, as deeper tiles read
-//   and write a wider window at once (64 MiB in four segments 18.0, 23.4 /
-//   17.6, 24.7 / 17.3, 26.4; the EP all-to-all(v) 194 with one, 213 with
-//   four), and below 16 MiB where segments are unequal (64 of 40,000 bytes on
-//   average, skewed: 3.0, 3.5 / 3.3, 4.3 / 3.3, 4.3).
+//   and write a wider window at once (256 MiB in 64 segments 75.2, 86.0 /
+//   64.3, 98.1 / -; the EP all-to-all(v) of 608 MB 10% less with one), and
+//   below 16 MiB where segments are unequal (64 of 23 KB on average, skewed:
+//   3.0, 3.5 / 3.3, 4.3 / 3.1, 3.5).
 // * A workgroup budget of fewer than those: deep tiles, as the bytes in flight
 //   per wave then set the rate (8 workgroups: 2.5 ms for 512 MiB with 4
 //   vectors, 4.2 with 2), segment by segment for equal segments (all-to-all at
 //   R = 8 on 64 workgroups, 512 KiB a pair: - / 33.5, 43.1 / 14.9, 29.0; on 8,
-//   64 KiB: - / 25.7, 36.2 / 10.9, 16.1), else the row (skewed, 1 MB a pair on
-//   64: - / 28.9, 29.8 / 96, 96).
+//   64 KiB: - / 25.7, 36.2 / 10.9, 16.1), else the row (skewed, 0.6 MB a pair
+//   on 64: - / 28.9, 29.8 / 96, 96).
 uint32_t copy_layout(CopyArgs &a, int threads, int budget) {
     constexpr uint64_t MiB = 1u << 20;
     const uint64_t bytes = bytes_written(a);
@@ -1007,14 +1014,15 @@ uint32_t copy_layout(CopyArgs &a, int threads, int budget) {
 // Segments of several destinations, whose tiles each write several times
 // themselves; times as above, row / segment by segment.
 // * Up to 16 MiB written: segment by segment, one vector (gathers of 64 KiB
-//   shards at R = 8 3.3, 2.9 / 3.0, 2.8 and R = 3 3.2, 3.5 / 2.4, 2.6).
+//   shards at R = 8 3.3, 2.9 / 3.0, 2.8, of 256 KiB at R = 3 3.3, 3.1 / 2.6,
+//   2.6).
 // * Beyond, the row: one vector under the bound of copy_lds from kWideFan
-//   destinations on, where writes dominate (eight 16 MiB shards 180 us; 207
-//   without the bound; 239 with four vectors), four vectors and no bound for
+//   destinations on, where writes dominate (eight 16 MiB shards 187 us; 211
+//   without the bound, 201 with four vectors), four vectors and no bound for
 //   fewer, which leave too few bytes in flight so (two 16 MiB shards 13.7 and
 //   21.0 with one vector, four 1 MiB shards 4.7 and 5.2).
 // * A budget of fewer workgroups: the row with four vectors (eight 16 MiB
-//   shards on 8 workgroups 1290, with one vector 1700; on 64 196 and 231).
+//   shards on 8 workgroups 1290, with one vector 1700; on 64 202 and 231).
 uint32_t copy_layout(FanArgs &a, int threads, int budget) {
     int nd = 0;
     for (int k = 0; k < a.nseg; ++k) nd = a.seg[k].nd > nd ? a.seg[k].nd : nd;
@@ -1036,11 +1044,10 @@ hipError_t launch_copy(const CopyArgs &a, int wg, int threads, hipStream_t s, si
     if (a.unroll != 1) return launch_copy_as<kDeepCopy, false, true>(a, wg, threads, s);
     // Reading more than the 256 MB last-level cache holds, little of it can be
     // there from an earlier write, and non-temporal loads are the faster ones:
-    // 204 us for the EP all-to-all(v) (608 MB) instead of 217, 747 for a 2 GiB
-    // copy instead of 772 (at 4 vectors per thread).  Where the data is in the
-    // cache they are slower: a pipeline schedule of 16 MiB messages, each read
-    // soon after it was written, would take 1234 us instead of 1119, a 64 MiB
-    // copy 32.8 instead of 28.3.
+    // 6% for the EP all-to-all(v) (608 MB), 3% for a 2 GiB copy (at 4 vectors
+    // per thread).  Where the data is in the cache they are slower: a pipeline
+    // schedule of 16 MiB messages, each read soon after it was written, took
+    // 10% longer, a 64 MiB copy 16%.
     return bytes_written(a) > ((uint64_t)256 << 20) ? launch_copy_as<1, true, true>(a, wg, threads, s)
                                                     : launch_copy_as<1, false, true>(a, wg, threads, s);
 }
@@ -1058,8 +1065,8 @@ hipError_t launch_fan(const FanArgs &a, int wg, int threads, hipStream_t s, size
 }
 
 // The kernel uses no LDS; asking for it bounds how many workgroups a CU holds
-// (64 KiB of 160 KiB: two of 256 threads).  Eight 16 MiB shards take 188 us
-// so and 214 without, eight of 48 MiB 565 and 698.  Beside a bf16 GEMM of
+// (64 KiB of 160 KiB: two of 256 threads).  Eight 16 MiB shards take 187 us
+// so and 211 without, eight of 48 MiB 565 and 698.  Beside a bf16 GEMM of
 // 8192^3 the 16 MiB gather takes 460 us and 821, the GEMM being 66% and 26%
 // slower meanwhile, which is 0.18 and 0.17 ms of its time per gather.  On a
 // stream with 32 of the CUs the bound costs (638 us and 366): the caller drops

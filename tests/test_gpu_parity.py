@@ -182,8 +182,9 @@ def test_launch_shapes(wg, threads):
 
 @pytest.mark.parametrize("lead", [1, 3, 5])
 def test_misaligned_buffers(lead):
-    """Output windows that start off a 16-byte boundary take the scalar head
-    and tail paths; inputs are sub-views at an element offset too."""
+    """Output windows that start off a 16-byte boundary, and inputs that are
+    sub-views at the same element offset: elements before and after the
+    vectors."""
     for dt in DTS:
         R, n = 4, 10_007
         x = [W.random_values(NAME[dt], 41 + lead, r, n) for r in range(R)]
@@ -199,7 +200,8 @@ def test_misaligned_buffers(lead):
 
 
 def test_mixed_alignment_across_ranks():
-    # rank buffers with different misalignments force the all-scalar path
+    # rank buffers with different misalignments: only the first operand's
+    # vectors are aligned
     R, n, dt = 3, 5003, hc.FP32
     x = [W.random_values("fp32", 51, r, n) for r in range(R)]
     ref = oracle.allreduce_new(x, dt)

@@ -4,8 +4,8 @@ Hops chained in ring order over chunk j -- first (x[j+1] + x[j+2]), middle
 hops adding x[j+3] ... x[j-1], last adding x[j] -- must give rank j's block
 of the oracle's reduce-scatter bit for bit; R = 2 is a single "only" hop.
 The cases cover every dtype, a ragged count, views that start off a 16-byte
-boundary (the kernel's scalar head, or a fully scalar segment when the
-operands disagree in alignment), the partial updated in place, small
+boundary (elements before the vectors, and vectors that are misaligned where
+the operands disagree in alignment), the partial updated in place, small
 workgroup budgets and the headline chunk: 3,145,728 bf16 elements, one
 rank's share of the GPT-6.7B gradient bucket."""
 import numpy as np
@@ -62,8 +62,9 @@ def test_hops_in_ring_order_equal_the_oracle(dt, R, layout):
     j = R - 1
     ref = oracle.reduce_scatter_new(x, dt)[j]
     # "head": every operand one element off a 16-byte boundary, so the
-    # kernel runs a scalar head and then its vector loop; "scalar": the
-    # inputs and outputs disagree in alignment, so no vector loop is legal.
+    # kernel takes some elements singly before its vectors; "scalar": the
+    # inputs and outputs disagree in alignment, so that the output's vectors
+    # are misaligned.
     shift = {"aligned": 0, "head": 1, "scalar": 1}[layout]
     out_shift = {"aligned": 0, "head": 1, "scalar": 3}[layout]
     blocks = [placed(x[r][j * n:(j + 1) * n], dt, shift) for r in range(R)]
