@@ -591,13 +591,13 @@ __device__ __forceinline__ const A &kernargs() {
     return *(const A *)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
-template <class T, int VE, int NR, int CAP, bool RH>
+template <class T, int VE, int NR, int CAP, bool RH, bool IN_TURN = false>
 __global__ void __launch_bounds__(1024) fold_kernel(FoldArgsT<CAP>) {
     const FoldArgsT<CAP> &a = kernargs<FoldArgsT<CAP>>();
     // Forced inline: for_each_segment calls the body from two places, and
     // the eight-rank rounding fold was otherwise left an out-of-line call
     // with a scratch frame.
-    for_each_segment<false>(a.R, false, [&](int j, int lb, int nb) __attribute__((always_inline)) {
+    for_each_segment<IN_TURN>(a.R, false, [&](int j, int lb, int nb) __attribute__((always_inline)) {
         fold_chunk<T, VE, NR, RH>(a, j, lb, nb);
     });
 }
@@ -901,6 +901,22 @@ size_t fold_elems_per_thread(hoccl_dtype_t dt) { return 16 / dtype_size(dt); }
 // wave has.
 template <class T, int VE, int NR, bool RH>
 static hipError_t launch_fold_r(const FoldArgs &a, int wg, int threads, hipStream_t s, size_t lds) {
+    // Beyond 600 MiB a rank, folds of 4 and 8 ranks take their blocks in turn,
+    // and of two ranks beyond 768 MiB: runs of blocks, which are the faster ones
+    // below, lose to it there (bf16, us, runs and in turn over the same buffers):
+    //   reduce-scatter  R = 8  384 MiB 652 and 688, 1 GiB 2010 and 1840, 2 GiB 4370
+    //     and 3720;  R = 4  384 MiB 397 and 408, 1280 MiB 1555 and 1297, 2 GiB
+    //     2796 and 2178;  R = 2  640 MiB 402 and 425, 1 GiB 675 and 625
+    //   all-reduce  R = 8  384 MiB 1208 and 1270, 1 GiB 3530 and 3340;  R = 4  448
+    //     MiB 723 and 809, 1536 MiB 2990 and 2565;  R = 2  640 MiB 532 and 568, 1
+    //     GiB 855 and 793
+    // Between 512 and 600 MiB it goes by the size; three, six and 16 ranks take
+    // as long either way.
+    if constexpr (NR == 2 || NR == 4 || NR == 8) {
+        const uint64_t bytes = a.total * sizeof(typename T::S);
+        if (bytes > ((uint64_t)(NR == 2 ? 768 : 600) << 20))
+            return launch((const void *)fold_kernel<T, VE, NR, NR, RH, true>, fit<NR>(a), wg, threads, s, lds);
+    }
     return launch((const void *)fold_kernel<T, VE, NR, NR, RH>, fit<NR>(a), wg, threads, s, lds);
 }
 
