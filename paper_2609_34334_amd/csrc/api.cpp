@@ -390,6 +390,8 @@ int auto_workgroups(const DeviceState &st, const hoccl_config_t &cfg, const Plan
 // mask that leaves some out.
 bool whole_chip(const DeviceState &st, hipStream_t s) {
     uint32_t mask[16] = {};
+    // The runtime's own handles stand for streams without a mask of their own.
+    if (s == hipStreamLegacy || s == hipStreamPerThread) s = nullptr;
     if (hipExtStreamGetCUMask(s, 16, mask) != hipSuccess) return false;
     int cus = 0;
     for (uint32_t m : mask) cus += __builtin_popcount(m);

@@ -9,6 +9,7 @@ chip and choose their own workgroups; everything else must not."""
 import ctypes
 import os
 import time
+import types
 
 import numpy as np
 import pytest
@@ -127,3 +128,19 @@ def test_bounded_launches_on_whole_and_masked_streams(cus):
     whole = np.concatenate(shards)
     for r in range(6):
         assert_bitwise(from_dev(out[r], hc.UINT8), whole, f"AG r={r}")
+
+
+def test_bounded_launch_on_the_per_thread_stream():
+    """The handle 2 (hipStreamPerThread) is no pointer: asking for its mask must
+    not follow it."""
+    R, n = 3, (4 << 20) + 3
+    x = [W.random_values("fp32", 1040, r, n) for r in range(R)]
+    send = [to_dev(a, hc.FP32) for a in x]
+    out = [torch.empty_like(t) for t in send]
+    hc.set_config(reduce_algo="direct")
+    torch.cuda.synchronize()
+    hc.allreduce(send, out, stream=types.SimpleNamespace(cuda_stream=2))
+    torch.cuda.synchronize()
+    ref = oracle.allreduce_new(x, hc.FP32)
+    for r in range(R):
+        assert_bitwise(from_dev(out[r], hc.FP32), ref[r], f"AR r={r}")
