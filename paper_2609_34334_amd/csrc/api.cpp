@@ -681,8 +681,8 @@ void flows_of(const Plan &p, const Buffers &B, int level, std::vector<Flow> &out
 // shard, a broadcast's buffer) go into segments of up to kMaxFan destinations
 // each, as even as they can be, so that a source is read once per segment and
 // no destination is left over for a launch of its own (the gather of nine 4 KiB
-// shards: 4.5 us with the ninth destination in a second launch, 2.8 in one; of
-// nine 256 KiB shards 7.4 and 5.2).  `wg` is raised to the most workgroups of
+// shards: 4.5 us with the ninth destination in a second launch, 2.4 in one; of
+// nine 256 KiB shards 7.5 and 5.8).  `wg` is raised to the most workgroups of
 // any launch here, `unread` by the bytes that sharing saves the plan's reads.
 hoccl_status_t run_copies_kernel(DeviceState &st, const hoccl_config_t &cfg, const Plan &p,
                                  const Buffers &B, hipStream_t s, int &wg, int threads,
