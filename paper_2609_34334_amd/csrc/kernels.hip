@@ -953,8 +953,21 @@ static hipError_t launch_fold_t(const FoldArgs &a, int wg, int threads, hipStrea
     case 6: return launch_fold_r<T, VE, 6, RH>(a, wg, threads, s, lds);
     case 7: return launch_fold_r<T, VE, 7, RH>(a, wg, threads, s, lds);
     case 8: return launch_fold_r<T, VE, 8, RH>(a, wg, threads, s, lds);
-    default: return launch((const void *)fold_kernel<T, VE, 0, kMaxRanks, RH>, a, wg, threads, s, lds);
     }
+    // A bf16 all-reduce of 16, 24, 32, ... ranks takes its blocks in turn, from
+    // 192 MiB of inputs on: each chunk then stays on one XCD, and R streams to
+    // write beside R to read lose less to each other.  Over the same buffers, in
+    // turn against runs of blocks: R = 16  32 MiB a rank 0.90, 48 MiB 0.92 (313 us
+    // and 340), 64 MiB 0.85, other sizes 0.96 to 1.04;  R = 24  16, 24 and 48 MiB
+    // 0.89 to 0.92, others to 1.03;  R = 32  16 MiB 0.88, others to 1.00.  Less
+    // gains nothing (R = 16, 8 MiB 1.08, 4 MiB 0.97), other rank counts lose (R =
+    // 12, 14, 20: 1.00 to 1.12, one point at 0.92), and so does fp32 at R = 16
+    // (0.86 to 1.16, 1.02 in the mean).
+    if constexpr (sizeof(typename T::S) == 2) {
+        if (a.write_all && a.R % kXcds == 0 && (uint64_t)a.R * a.total * 2 >= ((uint64_t)192 << 20))
+            return launch((const void *)fold_kernel<T, VE, 0, kMaxRanks, RH, true>, a, wg, threads, s, lds);
+    }
+    return launch((const void *)fold_kernel<T, VE, 0, kMaxRanks, RH>, a, wg, threads, s, lds);
 }
 
 hipError_t launch_fold(hoccl_dtype_t dt, const FoldArgs &a, int wg, int threads, hipStream_t s,
